@@ -32,13 +32,35 @@ __device__ __forceinline__ uint64_t init_counter(uint64_t g, int n, int i, int c
 }
 
 // Standard normal for noise injection (Eq. 10): Box-Muller on two 24-bit
-// uniforms of one draw from the keyed stream.
+// uniforms of one draw from the keyed stream.  Noise-injected sampling is
+// bound by the VALU work of this function, so it is written for its own
+// arguments only, with the same values as sqrtf(-2 logf(u1)) cosf(2 pi u2) for
+// every one of the 2^24 u1 and u2:
+//  - ln u = log2 u * ln 2 with ln 2 in two floats (the hardware log2, a product
+//    and its exact remainder); u1 is in [2^-24, 1], so there is no denormal or
+//    infinity to look for (22 -> 5 operations with the library's logf);
+//  - sqrt by one correction of x rsq(x) from its exact residual, x in
+//    [0, 33.3]; the bound on rsq makes sqrt(0) = 0 (20 -> 6);
+//  - the angle is below 2 pi, which is stated to the compiler: it drops the
+//    cosine's reduction of large arguments (132 -> 31), and with it most of
+//    the code whose 42 copies (one per spin of a generated kernel) did not fit
+//    the instruction cache.
 constexpr uint64_t kNoiseKey = 0xd1b54a32d192ed03ull;
 __device__ __forceinline__ float noise_value(uint64_t seed, uint64_t idx) {
-    uint64_t bits = splitmix64(seed ^ kNoiseKey, idx);
-    float u1 = (float)((uint32_t)(bits >> 40) + 1u) * 0x1p-24f;
-    float u2 = (float)(uint32_t)(bits & 0xffffffu) * 0x1p-24f;
-    return sqrtf(-2.0f * logf(u1)) * cosf(6.2831853071795864769f * u2);
+    const uint64_t bits = splitmix64(seed ^ kNoiseKey, idx);
+    const float u1 = (float)((uint32_t)(bits >> 40) + 1u) * 0x1p-24f;
+    const float u2 = (float)(uint32_t)(bits & 0xffffffu) * 0x1p-24f;
+    const float l2 = __builtin_amdgcn_logf(u1);
+    const float ln2h = 0x1.62e42ep-1f, ln2l = 0x1.efa39ep-25f;  // ln 2 = ln2h + ln2l
+    const float pr = l2 * ln2h;
+    const float ln = pr + fmaf(l2, ln2l, fmaf(l2, ln2h, -pr));
+    const float x = -2.0f * ln;
+    const float rs = fminf(fabsf(__builtin_amdgcn_rsqf(x)), 0x1p60f);
+    const float s0 = x * rs;
+    const float radius = fmaf(fmaf(-s0, s0, x), 0.5f * rs, s0);
+    const float angle = 6.2831853071795864769f * u2;
+    __builtin_assume(fabsf(angle) < 131072.0f);
+    return radius * cosf(angle);
 }
 
 // sgn with sgn(0) = +1 (x is never -0 in these dynamics).

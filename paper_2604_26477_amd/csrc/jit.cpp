@@ -87,13 +87,22 @@ __device__ __forceinline__ float initv(u64 seed, u64 idx, float amp) {
 }
 )";
 
-// Box-Muller on two 24-bit uniforms of one draw from the noise-keyed stream.
+// Box-Muller on two 24-bit uniforms of one draw from the noise-keyed stream:
+// the arithmetic of noise_value (device_common.hpp), which says why it is
+// written out.
 static const char *kNoisePrelude = R"(extern "C" __device__ float __ocml_cos_f32(float);
 __device__ __forceinline__ float nzv(u64 seed, u64 idx) {
   u64 b = sm64(seed ^ 0xd1b54a32d192ed03ull, idx);
   float u1 = (float)((u32)(b >> 40) + 1u) * 0x1p-24f;
   float u2 = (float)(u32)(b & 0xffffffull) * 0x1p-24f;
-  return __builtin_sqrtf(-2.0f * __builtin_logf(u1)) * __ocml_cos_f32(6.2831853071795864769f * u2);
+  float l2 = __builtin_amdgcn_logf(u1), h = 0x1.62e42ep-1f, l = 0x1.efa39ep-25f;
+  float pr = l2 * h;
+  float x = -2.0f * (pr + __builtin_fmaf(l2, l, __builtin_fmaf(l2, h, -pr)));
+  float rs = __builtin_fminf(__builtin_fabsf(__builtin_amdgcn_rsqf(x)), 0x1p60f);
+  float s0 = x * rs;
+  float angle = 6.2831853071795864769f * u2;
+  __builtin_assume(__builtin_fabsf(angle) < 131072.0f);
+  return __builtin_fmaf(__builtin_fmaf(-s0, s0, x), 0.5f * rs, s0) * __ocml_cos_f32(angle);
 }
 )";
 
