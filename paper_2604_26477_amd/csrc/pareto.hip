@@ -1,49 +1,46 @@
 // Non-dominated filtering of a sample pool (section "Pareto filtering",
 // dominance of Eq. 4 in cut / maximisation space) with duplicate merging.
 // A sampler's pool repeats the same cuts many times (at the 42-node
-// four-objective workload, 10.24 M rows hold about ten thousand distinct
-// vectors), so duplicates go first.
+// four-objective workload, 10.24 M rows hold about sixteen thousand distinct
+// vectors), so duplicates go first, and what is left is usually short enough
+// to compare every pair.
 //
 // 1. Duplicate merging.  Every row looks its vector up in an open-addressing
 //    hash table; each distinct vector ends with one slot holding its smallest
 //    sample index (the representative).  Rows are first merged per chunk of
-//    1024 in an LDS table, so that only each chunk's distinct vectors reach
-//    the global one.  The occupied slots are compacted into the list of
-//    distinct vectors.
-// 2. Pivots.  On an evenly strided sample of that list, the row with the
-//    largest normalised weighted sum is taken for each of 256 fixed positive
-//    directions (a maximiser of a positive weighted sum is non-dominated, so
-//    the pivots sit on or near the front).
-// 3. Pruning.  A listed row is dropped when some pivot p is >= it
-//    componentwise and either differs from it or has a smaller sample index.
-//    Such a row is dominated, or equal to an earlier row, so it is neither on
-//    the front nor a representative; every representative of the front
-//    survives, and every dominated survivor keeps a surviving dominator (the
-//    representative of a front vector above it), so filtering the survivors
-//    gives the pool's answer.  The survivors' per-objective ranges are
-//    reduced on the way.
-// 4. Order the survivors lexicographically descending: one stable radix sort
-//    per objective, last objective first, on the key (max_k - y_k) of only as
-//    many 8-bit digits as the survivors' range of objective k needs.  This
-//    order is a linear extension of dominance (y' dominates y => y' >lex y).
-// 5. Chunk pass: within chunks of 1024 consecutive (distinct) vectors, a
-//    vector is dropped when an earlier one in its chunk is >= it
-//    componentwise.
-// 6. Global pass over the chunk survivors: a survivor is kept when no earlier
-//    survivor is >= it componentwise.  Any dominator of it in an earlier
-//    chunk is itself dominated-or-equal by a survivor of that chunk, so
-//    comparing survivors with survivors is complete.  Early exit per block.
-//    Lists of at most 32768 vectors skip 5 and 6: every pair of 256-row
-//    tiles is one work item of a persistent grid that marks each vector with
-//    an earlier vector >= it componentwise.
-// 7. The kept sample indices are emitted in ascending order by a flagged
-//    compaction over 0..M-1.
-// The non-dominated ranks take steps 4-6 over every row (no merging or
-// pruning; equal vectors become adjacent, smallest index first, and the first
-// of each run represents it).
+//    1008 in an LDS table, so that only each chunk's distinct vectors reach
+//    the global one.  The occupied slots are collected into the list of distinct vectors
+//    (in no particular order; nothing below needs one).
+// 2. Lists longer than kPairMax only: pivots and pruning.  On an evenly
+//    strided sample of the list, the row with the largest normalised weighted
+//    sum is taken for each of 256 fixed positive directions (a maximiser of a
+//    positive weighted sum is non-dominated, so the pivots sit on or near the
+//    front), and a row is dropped when some other pivot is >= it
+//    componentwise.  If more than kPairMax rows are left, each chunk of 1024
+//    then drops the rows that another row of the chunk dominates.  Both only
+//    drop dominated rows, and every dominated row keeps a dominator (a front
+//    vector above it is never dropped), so the rest has the pool's front.
+// 3. Packing.  The listed vectors as 32-bit offsets from the first one, in
+//    list order; offsets that do not fit raise a flag.
+// 4. Pairs.  Every pair of 256-row tiles is one work item of a persistent
+//    grid: a row is marked when another row is >= it componentwise (the
+//    vectors are distinct, so that is dominance).
+// 5. The unmarked rows' sample indices go into a bitmap over 0..M-1 and are
+//    emitted in ascending order.
+// Nothing is sorted: a sort by objective costs three launches per digit, all
+// of which must be queued before the list length is known (96 launches, 0.5 ms
+// of the 1.1 ms that the headline pool took), to save half of the comparisons
+// (10 us of them).
+// The non-dominated ranks sort every row lexicographically descending (no
+// merging or pruning; equal vectors become adjacent, smallest index first, and
+// the first of each run represents it), a linear extension of dominance, and
+// peel the unique list with order-dependent passes: within chunks of 1024, a
+// row is dropped when an earlier one is >= it, then survivors against earlier
+// survivors; at most kPairMax rows take tile pairs (it <= jt) instead.
 // Every step runs on the caller's stream and every count stays on the device
-// (radix.hip: launches whose pass or tile is not needed return at once).
+// (launches that the list length does not need return at once).
 #include <climits>
+#include <type_traits>
 
 #include "radix.hpp"
 
@@ -55,8 +52,11 @@ constexpr int kB = 256;
 constexpr int kChunk = 1024;
 constexpr int kDirs = 256;          // pivot directions
 constexpr int kSampleRows = 1 << 17;  // rows of the pivot sample (at most)
-constexpr int kCandBlocks = 128;     // blocks of the pivot search
-constexpr int64_t kPairMax = 1 << 15;  // longest list of the pair pass (128 tiles)
+constexpr int kCandBlocks = 512;     // blocks of the pivot search (at most)
+// Longest list that goes to the pair pass as it is: at 20 000 vectors of four
+// objectives (the headline pool) its 4e8 pairs take 0.1 ms, and pruning first
+// left 16 700 of them, which saved less than its own kernels took.
+constexpr int64_t kPairMax = 1 << 15;
 constexpr int kPairBlocks = 2048;      // persistent grid of the pair pass
 
 unsigned grid_for_n(int64_t n, int per) {
@@ -110,13 +110,17 @@ __device__ __forceinline__ void sample_plan(int64_t n, int64_t &stride, int64_t 
     ns = (n + stride - 1) / stride;
 }
 
-// Per-objective range of the sample rows.
-template <int MM>
+// Per-objective range of the sample rows (SAMPLE; lists of at most kPairMax
+// rows are not pruned and need none) or of every row.
+template <int MM, bool SAMPLE>
 __global__ __launch_bounds__(kB) void sample_range_kernel(const int64_t *__restrict__ obj, RowList L,
                                                           int64_t *__restrict__ lo, int64_t *__restrict__ hi) {
     __shared__ int64_t rl[MM][kB], rh[MM][kB];
-    int64_t stride, ns;
-    sample_plan(L.n(), stride, ns);
+    int64_t stride = 1, ns = L.n();
+    if (SAMPLE) {
+        if (ns <= kPairMax) return;
+        sample_plan(L.n(), stride, ns);
+    }
     int64_t a[MM], b[MM];
 #pragma unroll
     for (int k = 0; k < MM; ++k) {
@@ -153,13 +157,15 @@ __global__ __launch_bounds__(kB) void sample_range_kernel(const int64_t *__restr
 }
 
 // Block b scans its share of the sample; thread d keeps the best row of
-// direction d (largest score, then smallest row index).
+// direction d (largest score, then smallest row index) and offers it to
+// best[d] as (score bits, ~row): scores are >= 0, so their bits order them.
 template <int MM>
 __global__ __launch_bounds__(kB) void pivot_cand_kernel(const int64_t *__restrict__ obj, RowList L,
                                                         const int64_t *__restrict__ lo, const int64_t *__restrict__ hi,
-                                                        float *__restrict__ cscore, int32_t *__restrict__ cidx) {
+                                                        unsigned long long *__restrict__ best_of) {
     __shared__ float yn[kB][MM];
     __shared__ int32_t yi[kB];
+    if (L.n() <= kPairMax) return;
     int64_t stride, ns;
     sample_plan(L.n(), stride, ns);
     float w[MM];
@@ -197,140 +203,105 @@ __global__ __launch_bounds__(kB) void pivot_cand_kernel(const int64_t *__restric
         }
         __syncthreads();
     }
-    cscore[(int64_t)blockIdx.x * kB + threadIdx.x] = best;
-    cidx[(int64_t)blockIdx.x * kB + threadIdx.x] = bidx;
+    if (best >= 0.0f)
+        atomicMax(&best_of[threadIdx.x],
+                  ((unsigned long long)__float_as_uint(best) << 32) | (uint32_t)~(uint32_t)bidx);
 }
 
-// One block: the best candidate of each direction over the candidate blocks,
-// distinct rows only, copied into the pivot table; np = their count.
-template <int MM>
-__global__ __launch_bounds__(kB) void pivot_reduce_kernel(const int64_t *__restrict__ obj,
-                                                          const float *__restrict__ cscore,
-                                                          const int32_t *__restrict__ cidx, int nblocks,
-                                                          int64_t *__restrict__ piv, int32_t *__restrict__ pidx,
-                                                          int64_t *__restrict__ np) {
-    __shared__ int32_t sel[kB];
-    __shared__ int32_t slot[kB];
-    float best = -1.0f;
-    int32_t bidx = INT32_MAX;
-    for (int b = 0; b < nblocks; ++b) {
-        const float s = cscore[(int64_t)b * kB + threadIdx.x];
-        const int32_t i = cidx[(int64_t)b * kB + threadIdx.x];
-        if (s > best || (s == best && i < bidx)) {
-            best = s;
-            bidx = i;
-        }
-    }
-    sel[threadIdx.x] = bidx;
-    __syncthreads();
-    bool first = bidx != INT32_MAX;
-    for (int t = 0; t < (int)threadIdx.x && first; ++t) first = sel[t] != bidx;
-    slot[threadIdx.x] = first ? 1 : 0;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int c = 0;
-        for (int t = 0; t < kB; ++t) {
-            const int f = slot[t];
-            slot[t] = f ? c : -1;
-            c += f;
-        }
-        *np = c;
-    }
-    __syncthreads();
-    const int p = slot[threadIdx.x];
-    if (p >= 0) {
-        pidx[p] = bidx;
-#pragma unroll
-        for (int k = 0; k < MM; ++k) piv[(int64_t)p * MM + k] = obj[(int64_t)bidx * MM + k];
-    }
+// Appends `value` of the lanes with `mine` to out[*count ..], one atomic per wave.
+template <typename T>
+__device__ __forceinline__ void wave_append(bool mine, T value, T *__restrict__ out, int64_t *__restrict__ count) {
+    const uint64_t mask = __ballot(mine);
+    if (mask == 0) return;
+    const int lane = threadIdx.x & 63, leader = __ffsll((unsigned long long)mask) - 1;
+    unsigned long long base = 0;
+    if (lane == leader) base = atomicAdd((unsigned long long *)count, (unsigned long long)__popcll(mask));
+    base = __shfl(base, leader);
+    if (mine) out[base + __popcll(mask & ((1ull << lane) - 1ull))] = value;
 }
 
-// flag[i] = 1 unless a pivot is >= row L.row(i) componentwise and differs
-// from it or has a smaller index; the kept rows' per-objective range goes to
-// lo / hi.
+// Appends the listed rows that no pivot dominates.  A block takes 64 rows at a
+// time and each of its four waves a quarter of the pivots, so that a list of a
+// few ten thousand rows fills the GPU.
 template <int MM>
 __global__ __launch_bounds__(kB) void prune_kernel(const int64_t *__restrict__ obj, RowList L,
-                                                   const int64_t *__restrict__ piv, const int32_t *__restrict__ pidx,
-                                                   const int64_t *__restrict__ d_np, uint8_t *__restrict__ flag,
-                                                   int64_t *__restrict__ lo, int64_t *__restrict__ hi) {
+                                                   const unsigned long long *__restrict__ best_of,
+                                                   int32_t *__restrict__ out, int64_t *__restrict__ count) {
     __shared__ int64_t pv[kDirs][MM];
-    __shared__ int32_t pi[kDirs];
-    __shared__ int64_t rl[MM][kB], rh[MM][kB];
-    const int np = d_np ? (int)*d_np : 0;
+    __shared__ uint64_t hit[kB / 64];
     const int64_t n = L.n();
-    for (int p = threadIdx.x; p < np; p += kB) {
-        pi[p] = pidx[p];
+    if (n <= kPairMax) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // (a row may be the pivot of several directions)
+    const int32_t mine = (int32_t)~(uint32_t)best_of[threadIdx.x];
 #pragma unroll
-        for (int k = 0; k < MM; ++k) pv[p][k] = piv[(int64_t)p * MM + k];
-    }
+    for (int k = 0; k < MM; ++k) pv[threadIdx.x][k] = obj[(int64_t)mine * MM + k];
     __syncthreads();
-    int64_t a[MM], b[MM];
-#pragma unroll
-    for (int k = 0; k < MM; ++k) {
-        a[k] = INT64_MAX;
-        b[k] = INT64_MIN;
-    }
-    for (int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x; i < n; i += (int64_t)gridDim.x * kB) {
-        const int64_t r = L.row(i);
+    const int p0 = wave * 64, p1 = p0 + 64;
+    for (int64_t c = (int64_t)blockIdx.x * 64; c < n; c += (int64_t)gridDim.x * 64) {
+        const int64_t i = c + lane;
+        const bool live = i < n;
+        const int64_t r = live ? L.row(i) : 0;
         int64_t y[MM];
 #pragma unroll
-        for (int k = 0; k < MM; ++k) y[k] = obj[r * MM + k];
-        bool drop = false;
-        for (int p = 0; p < np && !drop; ++p) {
-            bool ge = true, ne = false;
+        for (int k = 0; k < MM; ++k) y[k] = live ? obj[r * MM + k] : 0;
+        bool drop = !live;
+        for (int p = p0; p < p1; ++p) {
+            bool ge = true, ne = false;  // the listed vectors are distinct: an equal pivot is the row itself
 #pragma unroll
             for (int k = 0; k < MM; ++k) {
                 ge &= pv[p][k] >= y[k];
                 ne |= pv[p][k] != y[k];
             }
-            drop = ge && (ne || pi[p] < r);
+            drop |= ge && ne;
+            if ((p & 7) == 7 && __ballot(!drop) == 0) break;
         }
-        flag[i] = drop ? 0 : 1;
-        if (!drop) {
-#pragma unroll
-            for (int k = 0; k < MM; ++k) {
-                a[k] = min(a[k], y[k]);
-                b[k] = max(b[k], y[k]);
-            }
+        const uint64_t dropped = __ballot(drop);
+        if (lane == 0) hit[wave] = dropped;
+        __syncthreads();
+        if (wave == 0) {
+            uint64_t all = 0;
+            for (int w = 0; w < kB / 64; ++w) all |= hit[w];
+            wave_append(((all >> lane) & 1ull) == 0, (int32_t)r, out, count);
         }
-    }
-#pragma unroll
-    for (int k = 0; k < MM; ++k) {
-        rl[k][threadIdx.x] = a[k];
-        rh[k][threadIdx.x] = b[k];
-    }
-    __syncthreads();
-    for (int s = kB / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s)
-#pragma unroll
-            for (int k = 0; k < MM; ++k) {
-                rl[k][threadIdx.x] = min(rl[k][threadIdx.x], rl[k][threadIdx.x + s]);
-                rh[k][threadIdx.x] = max(rh[k][threadIdx.x], rh[k][threadIdx.x + s]);
-            }
         __syncthreads();
     }
-    if ((int)threadIdx.x < MM) {
-        atomicMin((long long *)&lo[threadIdx.x], (long long)rl[threadIdx.x][0]);
-        atomicMax((long long *)&hi[threadIdx.x], (long long)rh[threadIdx.x][0]);
+}
+
+// Clears what a filter call starts from: the hash table (-1, sixteen bytes a
+// store), the bitmap of kept rows, the counts, the pivots and the sample range.
+__global__ __launch_bounds__(kB) void filter_init_kernel(int4 *__restrict__ table, int64_t table_quads,
+                                                         uint32_t *__restrict__ bits, int64_t words,
+                                                         int64_t *__restrict__ counts,
+                                                         unsigned long long *__restrict__ best_of,
+                                                         int64_t *__restrict__ lo, int64_t *__restrict__ hi) {
+    const int64_t t0 = (int64_t)blockIdx.x * kB + threadIdx.x, step = (int64_t)gridDim.x * kB;
+    for (int64_t i = t0; i < table_quads; i += step) table[i] = make_int4(-1, -1, -1, -1);
+    for (int64_t i = t0; i < words; i += step) bits[i] = 0u;
+    if (blockIdx.x == 0) {
+        best_of[threadIdx.x] = 0ull;
+        if (threadIdx.x < 8) {
+            counts[threadIdx.x] = 0;
+            lo[threadIdx.x] = INT64_MAX;
+            hi[threadIdx.x] = INT64_MIN;
+        }
     }
 }
 
-__global__ void fill_i32_kernel(int32_t *p, int64_t n, int32_t v) {
-    for (int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x; i < n; i += (int64_t)gridDim.x * kB) p[i] = v;
-}
-
-__device__ __forceinline__ uint64_t vec_hash_step(uint64_t h, int64_t y) {
-    h = (h ^ (uint64_t)y) * 0xFF51AFD7ED558CCDull;
-    return h ^ (h >> 32);
-}
-
+// 32-bit hash of a vector: one multiply per objective (its two words folded
+// first) and a final mix.  32-bit multiplies issue at a quarter of the rate,
+// 64-bit ones take three of them.
 template <int MM>
-__device__ __forceinline__ uint64_t vec_hash(const int64_t (&y)[MM]) {
-    uint64_t h = 0x243F6A8885A308D3ull;
+__device__ __forceinline__ uint32_t vec_hash(const int64_t (&y)[MM]) {
+    uint32_t h = 0x243F6A88u;
 #pragma unroll
-    for (int k = 0; k < MM; ++k) h = vec_hash_step(h, y[k]);
-    h = (h ^ (h >> 29)) * 0xC4CEB9FE1A85EC53ull;
-    return h ^ (h >> 32);
+    for (int k = 0; k < MM; ++k) {
+        const uint32_t lo = (uint32_t)y[k], hi = (uint32_t)((uint64_t)y[k] >> 32);
+        h = (h ^ lo ^ ((hi << 13) | (hi >> 19))) * 0x9E3779B1u;
+        h ^= h >> 15;
+    }
+    h *= 0x85EBCA77u;
+    return h ^ (h >> 13);
 }
 
 // Open addressing in the global table of `mask + 1` slots (more than the row
@@ -340,9 +311,9 @@ __device__ __forceinline__ uint64_t vec_hash(const int64_t (&y)[MM]) {
 // Slots never change vector, so every row of a vector reaches the same slot,
 // which ends holding the smallest row index offered for it.
 template <int MM>
-__device__ __forceinline__ void table_insert(const int64_t *__restrict__ obj, const int64_t (&y)[MM], uint64_t h,
-                                             int32_t me, int32_t *__restrict__ table, uint64_t mask) {
-    uint64_t s = h & mask;
+__device__ __forceinline__ void table_insert(const int64_t *__restrict__ obj, const int64_t (&y)[MM], uint32_t h,
+                                             int32_t me, int32_t *__restrict__ table, uint32_t mask) {
+    uint32_t s = h & mask;
     while (true) {
         int32_t q = table[s];
         if (q < 0) {
@@ -360,32 +331,39 @@ __device__ __forceinline__ void table_insert(const int64_t *__restrict__ obj, co
     }
 }
 
-constexpr int kDedupRows = 1024;   // rows per chunk of the in-block merge
-constexpr int kDedupSlots = 2048;  // its LDS hash slots
+// Duplicate merging in two levels.  A sampler's pool repeats its most frequent
+// cut vectors hundreds of thousands of times, and one global table slot per
+// vector made those rows queue on a few cache lines.  So each block first
+// merges a chunk of consecutive rows in an LDS table (the same probing, on the
+// chunk's vectors staged in LDS, keeping the smallest row of the chunk per
+// vector), and only the chunk's distinct vectors, with those rows, go to the
+// global table.  The global minimum over the chunks' minima is the vector's
+// smallest row.  Bound by latency, of the global inserts above all (a random
+// slot, then a random row): the chunk's distinct vectors are listed first, so
+// that one round of inserts, two at most, takes them all (a thread per eighth
+// of the LDS slots took eight rounds, nearly empty ones).
+constexpr int kDedupRows = 1008;   // rows per chunk: four blocks' LDS fit a CU at MM = 4
+constexpr int kDedupSlots = 2048;  // LDS hash slots
+constexpr int kDT = 512;           // threads per block: two rows each, 32 waves per CU
 
-// Duplicate merging in two levels.  A sampler's pool repeats its most
-// frequent cut vectors hundreds of thousands of times, and one global table
-// slot per vector made those rows queue on a few cache lines.  So each block
-// first merges a chunk of 1024 consecutive rows in an LDS table (the same
-// probing, on the chunk's vectors staged in LDS, keeping the smallest row of
-// the chunk per vector), and only the chunk's distinct vectors, with those
-// rows, go to the global table.  The global minimum over the chunks'
-// minima is the vector's smallest row.
 template <int MM>
-__global__ __launch_bounds__(kB) void dedupe_kernel(const int64_t *__restrict__ obj, int64_t M,
-                                                    int32_t *__restrict__ table, uint64_t mask) {
-    __shared__ int64_t v[kDedupRows][MM];
+__global__ __launch_bounds__(kDT) void dedupe_kernel(const int64_t *__restrict__ obj, int64_t M,
+                                                    int32_t *__restrict__ table, uint32_t mask) {
+    constexpr int SPT = kDedupSlots / kDT;  // slots per thread
+    __shared__ __attribute__((aligned(16))) int64_t v[kDedupRows][MM];
     __shared__ int32_t loc[kDedupSlots];
+    __shared__ int32_t have;
     for (int64_t c0 = (int64_t)blockIdx.x * kDedupRows; c0 < M; c0 += (int64_t)gridDim.x * kDedupRows) {
         const int len = (int)((M - c0) < kDedupRows ? (M - c0) : kDedupRows);
-        for (int i = threadIdx.x; i < kDedupSlots; i += kB) loc[i] = -1;
-        for (int i = threadIdx.x; i < len * MM; i += kB) (&v[0][0])[i] = obj[c0 * MM + i];
+        for (int i = threadIdx.x; i < kDedupSlots; i += kDT) loc[i] = -1;
+        if (threadIdx.x == 0) have = 0;
+        for (int i = threadIdx.x; i < len * MM; i += kDT) (&v[0][0])[i] = obj[c0 * MM + i];
         __syncthreads();
-        for (int p = threadIdx.x; p < len; p += kB) {
+        for (int p = threadIdx.x; p < len; p += kDT) {
             int64_t y[MM];
 #pragma unroll
             for (int k = 0; k < MM; ++k) y[k] = v[p][k];
-            uint32_t s = (uint32_t)vec_hash<MM>(y) & (kDedupSlots - 1);
+            uint32_t s = (vec_hash<MM>(y) >> 8) & (kDedupSlots - 1);
             while (true) {
                 int32_t q = loc[s];
                 if (q < 0) {
@@ -403,16 +381,391 @@ __global__ __launch_bounds__(kB) void dedupe_kernel(const int64_t *__restrict__ 
             }
         }
         __syncthreads();
-        for (int i = threadIdx.x; i < kDedupSlots; i += kB) {
-            const int32_t p = loc[i];
-            if (p < 0) continue;
+        // the occupied slots, listed in the slots' own memory
+        int32_t mine[SPT];
+        int c = 0;
+#pragma unroll
+        for (int u = 0; u < SPT; ++u) {
+            mine[u] = loc[u * kDT + threadIdx.x];
+            c += mine[u] >= 0;
+        }
+        int at = c > 0 ? atomicAdd(&have, c) : 0;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < SPT; ++u)
+            if (mine[u] >= 0) loc[at++] = mine[u];
+        __syncthreads();
+        const int n = have;
+        for (int i = threadIdx.x; i < n; i += kDT) {
+            const int p = loc[i];
             int64_t y[MM];
 #pragma unroll
             for (int k = 0; k < MM; ++k) y[k] = v[p][k];
             table_insert<MM>(obj, y, vec_hash<MM>(y), (int32_t)(c0 + p), table, mask);
         }
-        __syncthreads();  // v and loc are rewritten for the next chunk
+        __syncthreads();  // v, loc and have are rewritten for the next chunk
     }
+}
+
+// list[0 .. *count) = the rows named by the table's occupied slots, in no
+// particular order.  Bound by reading the table; a block collects what it finds
+// in LDS and takes one atomic per 4096 to 8192 rows (one per 4096 slots, all on
+// the same word, took 50 us for 2^24 slots).
+constexpr int kCollectBlocks = 512;
+__global__ __launch_bounds__(kB) void collect_kernel(const int4 *__restrict__ table, int64_t quads,
+                                                     int32_t *__restrict__ list, int64_t *__restrict__ count) {
+    constexpr int kPer = 16 * kB;  // slots per step
+    __shared__ int32_t buf[2 * kPer];
+    __shared__ int32_t have;
+    __shared__ int64_t base_sh;
+    if (threadIdx.x == 0) have = 0;
+    __syncthreads();
+    auto flush = [&]() {
+        const int nc = have;
+        if (threadIdx.x == 0 && nc > 0) base_sh = (int64_t)atomicAdd((unsigned long long *)count, (unsigned long long)nc);
+        __syncthreads();
+        for (int i = threadIdx.x; i < nc; i += kB) list[base_sh + i] = buf[i];
+        __syncthreads();
+        if (threadIdx.x == 0) have = 0;
+        __syncthreads();
+    };
+    const int64_t steps = (quads * 4 + kPer - 1) / kPer;
+    for (int64_t st = blockIdx.x; st < steps; st += gridDim.x) {
+        int32_t q[16];
+        int c = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t i = st * (kPer / 4) + u * kB + threadIdx.x;
+            const int4 v = i < quads ? table[i] : make_int4(-1, -1, -1, -1);
+            q[4 * u] = v.x;
+            q[4 * u + 1] = v.y;
+            q[4 * u + 2] = v.z;
+            q[4 * u + 3] = v.w;
+        }
+#pragma unroll
+        for (int u = 0; u < 16; ++u) c += q[u] >= 0;
+        if (c > 0) {
+            int at = atomicAdd(&have, c);
+#pragma unroll
+            for (int u = 0; u < 16; ++u)
+                if (q[u] >= 0) buf[at++] = q[u];
+        }
+        __syncthreads();
+        const int full = have > kPer;
+        __syncthreads();  // everybody has read `have` before the next step adds to it
+        if (full) flush();
+    }
+    flush();
+}
+
+// The list that the pair pass compares: every distinct vector when there are
+// at most kPairMax, else the rows left by pruning, or by the chunk pass when
+// pruning left more than kPairMax.
+struct PairList {
+    const int32_t *all;      // distinct vectors, counts[0] of them
+    const int32_t *pruned;   // left by pruning, counts[1] of them
+    const int32_t *chunked;  // left by the chunk pass, counts[2] of them
+    const int64_t *counts;
+    __device__ __forceinline__ int route() const {
+        return counts[0] <= kPairMax ? 0 : counts[1] <= kPairMax ? 1 : 2;
+    }
+    __device__ __forceinline__ const int32_t *list(int r) const { return r == 0 ? all : r == 1 ? pruned : chunked; }
+};
+
+// Chunk pass over a long pruned list, in any order: a row that another row of
+// its chunk of 1024 dominates is dropped, the others are appended.  Each thread
+// holds four rows in registers and walks the chunk once for all four (one
+// broadcast LDS read of a row serves four comparisons), stopping when all four
+// are dominated.
+template <int MM>
+__global__ __launch_bounds__(kB) void chunk_any_kernel(const int64_t *__restrict__ obj,
+                                                       const int32_t *__restrict__ list, const int64_t *counts,
+                                                       int32_t *__restrict__ out, int64_t *out_count) {
+    constexpr int RPT = kChunk / kB;  // rows per thread
+    __shared__ int64_t v[kChunk][MM];
+    const int64_t n = counts[1];
+    if (counts[0] <= kPairMax || n <= kPairMax) return;
+    for (int64_t c0 = (int64_t)blockIdx.x * kChunk; c0 < n; c0 += (int64_t)gridDim.x * kChunk) {
+        const int len = (int)((n - c0) < kChunk ? (n - c0) : kChunk);
+        for (int p = threadIdx.x; p < len; p += kB) {
+            const int64_t *y = obj + (int64_t)list[c0 + p] * MM;
+#pragma unroll
+            for (int k = 0; k < MM; ++k) v[p][k] = y[k];
+        }
+        __syncthreads();
+        int64_t y[RPT][MM];
+        bool dom[RPT];
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) {
+            const int j = r * kB + threadIdx.x;
+            dom[r] = j >= len;
+#pragma unroll
+            for (int k = 0; k < MM; ++k) y[r][k] = j < len ? v[j][k] : 0;
+        }
+        for (int i = 0; i < len; ++i) {
+            int64_t w[MM];
+#pragma unroll
+            for (int k = 0; k < MM; ++k) w[k] = v[i][k];
+            bool done = true;
+#pragma unroll
+            for (int r = 0; r < RPT; ++r) {
+                bool ge = i != r * kB + (int)threadIdx.x;
+#pragma unroll
+                for (int k = 0; k < MM; ++k) ge &= w[k] >= y[r][k];
+                dom[r] |= ge;
+                done &= dom[r];
+            }
+            if (done) break;
+        }
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) {
+            const int j = r * kB + threadIdx.x;
+            const bool left = j < len && !dom[r];
+            wave_append(left, left ? list[c0 + j] : 0, out, out_count);
+        }
+        __syncthreads();  // v is rewritten by the next chunk
+    }
+}
+
+// fin[i] = the i-th listed row, packed[i] = its vector as 32-bit offsets from
+// the first listed row's, dom[i] = 0; counts[3] = the list's length, counts[4]
+// = 1 when some offset does not fit.
+template <int MM>
+__global__ __launch_bounds__(kB) void pair_pack_kernel(const int64_t *__restrict__ obj, PairList L, int64_t *counts,
+                                                       int32_t *__restrict__ fin, int32_t *__restrict__ packed,
+                                                       uint8_t *__restrict__ dom) {
+    const int route = L.route();
+    const int64_t n = L.counts[route];
+    if (blockIdx.x == 0 && threadIdx.x == 0) counts[3] = n;
+    if (n == 0) return;
+    int64_t base[MM];
+    const int32_t *list = L.list(route);
+    const int64_t r0 = list[0];
+#pragma unroll
+    for (int k = 0; k < MM; ++k) base[k] = obj[r0 * MM + k];
+    bool wide = false;
+    for (int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x; i < n; i += (int64_t)gridDim.x * kB) {
+        const int64_t r = list[i];
+        fin[i] = (int32_t)r;
+        dom[i] = 0;
+#pragma unroll
+        for (int k = 0; k < MM; ++k) {
+            const int64_t y = obj[r * MM + k];
+            const uint64_t mag = y >= base[k] ? (uint64_t)y - (uint64_t)base[k] : (uint64_t)base[k] - (uint64_t)y;
+            wide |= mag > 0x3fffffffull;  // differences of two offsets fit 32 bits
+            packed[i * MM + k] = (int32_t)((uint64_t)y - (uint64_t)base[k]);
+        }
+    }
+    if (__ballot(wide) != 0 && (threadIdx.x & 63) == 0)
+        atomicMax((unsigned long long *)&counts[4], 1ull);  // 1, whoever sets it
+}
+
+// Pair pass: dom[j] = 1 when some other listed vector is >= vector j
+// componentwise.  ALU bound.  A work item is a tile of 256 rows j, one per
+// lane, against up to 256 rows i; a wave reads row i through scalar loads
+// (its address is uniform) and no LDS.  A pair takes MM subtractions with a
+// scalar operand, whose signs are ORed over the objectives and ANDed over the
+// rows i: MM + 2 vector instructions at MM = 4 (comparisons, each with its mask
+// in a scalar register pair and a scalar AND, took 2.5 times as long).  Items run i tile by i tile, so that
+// rows marked by the first tiles skip the later ones: a wave whose rows are all
+// marked stops.  Concurrent marks all store the same byte.  The 64-bit form,
+// for ranges past 32 bits, stages the rows i in LDS.
+template <int MM>
+__global__ __launch_bounds__(kB) void pair_any_kernel(const int64_t *__restrict__ obj, const int64_t *__restrict__ counts,
+                                                      const int32_t *__restrict__ fin,
+                                                      const int32_t *__restrict__ packed, uint8_t *dom) {
+    const int64_t n = counts[3];
+    const bool wide = counts[4] != 0;
+    const int64_t T = (n + kB - 1) / kB;
+    // rows i per item: all 256, fewer where the list alone would not fill the
+    // GPU (a chain of 256 rows is 11 us)
+    const int isz = n > 8192 ? kB : n > 2048 ? 64 : 32;
+    const int64_t TI = (n + isz - 1) / isz;
+    __shared__ int64_t v[kB][MM];
+    // item p = it * T + jt, stepped by the grid without a division per item
+    const int64_t step_it = gridDim.x / std::max<int64_t>(T, 1), step_jt = gridDim.x - step_it * T;
+    int64_t it = blockIdx.x / std::max<int64_t>(T, 1), jt = blockIdx.x - it * T;
+    for (; it < TI; it += step_it, jt += step_jt) {
+        if (jt >= T) {
+            jt -= T;
+            if (++it >= TI) break;
+        }
+        const int64_t i0 = it * isz;
+        const int64_t j = jt * kB + threadIdx.x;
+        bool done = j >= n || dom[j] != 0;
+        const int cnt = (int)((n - i0) < isz ? (n - i0) : isz);
+        const bool diag = i0 / kB == jt;  // some rows i are rows j
+        const int self = (int)(j - i0);
+        bool hit = false;
+        if (!wide) {
+            if (__ballot(!done) == 0) continue;
+            int32_t y[MM];
+#pragma unroll
+            for (int k = 0; k < MM; ++k) y[k] = j < n ? packed[j * MM + k] : 0;
+            const int32_t *q = packed + i0 * MM;
+            auto scan = [&](auto diagonal) __attribute__((always_inline)) {
+                constexpr bool DIAG = decltype(diagonal)::value;
+                int32_t miss = -1;  // sign bit set while every row has fallen short somewhere
+                auto test = [&](int t) __attribute__((always_inline)) {
+                    int32_t d = DIAG && t == self ? -1 : 0;
+#pragma unroll
+                    for (int k = 0; k < MM; ++k) d |= q[t * MM + k] - y[k];
+                    miss &= d;
+                };
+                int t = 0;
+                for (; t + 8 <= cnt; t += 8) {
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) test(t + u);
+                    if (__ballot(!done && miss < 0) == 0) break;
+                }
+                if (t + 8 > cnt)
+                    for (; t < cnt; ++t) test(t);
+                hit = miss >= 0;
+            };
+            if (diag) scan(std::true_type{});
+            else scan(std::false_type{});
+        } else {
+            if (!__syncthreads_or(done ? 0 : 1)) continue;
+            if ((int)threadIdx.x < cnt) {
+                const int64_t *y = obj + (int64_t)fin[i0 + threadIdx.x] * MM;
+#pragma unroll
+                for (int k = 0; k < MM; ++k) v[threadIdx.x][k] = y[k];
+            }
+            __syncthreads();
+            if (!done) {
+                const int64_t *y = obj + (int64_t)fin[j] * MM;
+                int64_t yj[MM];
+#pragma unroll
+                for (int k = 0; k < MM; ++k) yj[k] = y[k];
+                for (int t = 0; t < cnt && !hit; ++t) {
+                    bool ge = !diag || t != self;
+#pragma unroll
+                    for (int k = 0; k < MM; ++k) ge &= v[t][k] >= yj[k];
+                    hit = ge;
+                }
+            }
+            __syncthreads();  // v is rewritten by the next item
+        }
+        if (hit && !done) dom[j] = 1;
+    }
+}
+
+// Ascending emission, pools of at most kEmitSmall rows: one block builds the
+// bitmap of kept rows in LDS and writes the set bits in order.
+constexpr int64_t kEmitSmall = 1 << 16;
+__global__ __launch_bounds__(1024) void emit_small_kernel(const int32_t *__restrict__ fin,
+                                                          const uint8_t *__restrict__ dom,
+                                                          const int64_t *__restrict__ counts,
+                                                          int64_t *__restrict__ keep, int64_t *__restrict__ num) {
+    __shared__ uint32_t bits[kEmitSmall / 32];
+    __shared__ int32_t wsum[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    bits[tid] = 0u;
+    bits[tid + 1024] = 0u;
+    __syncthreads();
+    const int64_t n = counts[3];
+    for (int64_t i = tid; i < n; i += 1024)
+        if (dom[i] == 0) atomicOr(&bits[fin[i] >> 5], 1u << (fin[i] & 31));
+    __syncthreads();
+    const uint32_t w0 = bits[2 * tid], w1 = bits[2 * tid + 1];
+    const int c = __popc(w0) + __popc(w1);
+    int s = c;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(s, off);
+        if (lane >= off) s += o;
+    }
+    if (lane == 63) wsum[wave] = s;
+    __syncthreads();
+    int64_t at = s - c;
+    for (int w = 0; w < wave; ++w) at += wsum[w];
+    for (uint64_t b = (uint64_t)w0 | ((uint64_t)w1 << 32); b; b &= b - 1)
+        keep[at++] = (int64_t)tid * 64 + __ffsll((unsigned long long)b) - 1;
+    if (tid == 1023) *num = at;
+}
+
+// Larger pools: the bitmap is in device memory (mark), a tile of 16384 rows (64 per
+// thread) per block is counted, and each block adds up the tiles before its own
+// (or reads their scanned sum, when there are many) and writes its set bits.
+constexpr int64_t kEmitTile = 64 * kB;
+constexpr int64_t kEmitScan = 4096;  // tiles past which the counts are scanned by a launch of their own
+
+__global__ __launch_bounds__(kB) void mark_kernel(const int32_t *__restrict__ fin, const uint8_t *__restrict__ dom,
+                                                  const int64_t *__restrict__ counts, uint32_t *__restrict__ bits) {
+    const int64_t n = counts[3];
+    for (int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x; i < n; i += (int64_t)gridDim.x * kB)
+        if (dom[i] == 0) atomicOr(&bits[fin[i] >> 5], 1u << (fin[i] & 31));
+}
+
+__device__ __forceinline__ int block_sum(int v, int *sh) {
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    int s = 0;
+    for (int w = 0; w < kB / 64; ++w) s += sh[w];
+    __syncthreads();
+    return s;
+}
+
+__global__ __launch_bounds__(kB) void emit_count_kernel(const uint64_t *__restrict__ bits, int64_t words,
+                                                        uint32_t *__restrict__ cnt) {
+    __shared__ int sh[kB / 64];
+    const int64_t w = (int64_t)blockIdx.x * kB + threadIdx.x;
+    const int s = block_sum(w < words ? __popcll(bits[w]) : 0, sh);
+    if (threadIdx.x == 0) cnt[blockIdx.x] = (uint32_t)s;
+}
+
+// one block: exclusive scan of cnt[0 .. tiles) in place
+__global__ __launch_bounds__(kB) void emit_scan_kernel(uint32_t *__restrict__ cnt, int64_t tiles) {
+    __shared__ int sh[kB / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t carry = 0;
+    for (int64_t c = 0; c < tiles; c += kB) {
+        const int64_t i = c + threadIdx.x;
+        const int v = i < tiles ? (int)cnt[i] : 0;
+        int s = v;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(s, off);
+            if (lane >= off) s += o;
+        }
+        if (lane == 63) sh[wave] = s;
+        __syncthreads();
+        int pre = 0, total = 0;
+        for (int w = 0; w < kB / 64; ++w) {
+            if (w < wave) pre += sh[w];
+            total += sh[w];
+        }
+        if (i < tiles) cnt[i] = carry + (uint32_t)(pre + s - v);
+        carry += (uint32_t)total;
+        __syncthreads();
+    }
+}
+
+__global__ __launch_bounds__(kB) void emit_kernel(const uint64_t *__restrict__ bits, int64_t words,
+                                                  const uint32_t *__restrict__ cnt, bool scanned,
+                                                  int64_t *__restrict__ keep, int64_t *__restrict__ num) {
+    __shared__ int sh[kB / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int before = 0;
+    if (scanned) {
+        before = (int)cnt[blockIdx.x];
+    } else {
+        for (int t = threadIdx.x; t < (int)blockIdx.x; t += kB) before += (int)cnt[t];
+        before = block_sum(before, sh);
+    }
+    const int64_t w = (int64_t)blockIdx.x * kB + threadIdx.x;
+    uint64_t b = w < words ? bits[w] : 0ull;
+    const int c = __popcll(b);
+    int s = c;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(s, off);
+        if (lane >= off) s += o;
+    }
+    if (lane == 63) sh[wave] = s;
+    __syncthreads();
+    int64_t at = (int64_t)before + s - c;
+    for (int q = 0; q < wave; ++q) at += sh[q];
+    for (; b; b &= b - 1) keep[at++] = w * 64 + __ffsll((unsigned long long)b) - 1;
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == kB - 1) *num = at;
 }
 
 // Sort keys of objective k for the list of n = *d_n rows: key = hi_k - y_k
@@ -561,8 +914,8 @@ __global__ __launch_bounds__(kB) void global_nd_kernel(const int64_t *__restrict
     if (alive) keep[sidx[j]] = 1;
 }
 
-// Pair pass for lists of at most kPairMax vectors (the usual case once the
-// pivots have pruned a pool): the chunk and survivor passes above leave most
+// Pair pass of the ranks for lists of at most kPairMax vectors: the chunk and
+// survivor passes above leave most
 // CUs idle on a few thousand rows (one block per chunk, one per 256
 // survivors, each walking its earlier rows in sequence), so short lists are
 // instead split into 256-row tiles and every tile pair (it, jt) with
@@ -727,19 +1080,16 @@ __global__ __launch_bounds__(kB) void objective_min_kernel(const int64_t *__rest
 }
 
 
-// Workspace of the filter and of the ranks.  The first 64 bytes hold the
-// device counts: [0] unique vectors, [1] chunk survivors, [2] rows left after
-// pruning, [3] pivots.
+// Workspace of the ranks.  The first 64 bytes hold the device counts: [0]
+// unique vectors, [1] chunk survivors, [2] rows.
 struct PLayout {
-    size_t counts = 0, passes, lo, hi, slo, shi, piv, pidx, cscore, cidx;
+    size_t counts = 0, passes, lo, hi;
     size_t flag, keep, surv, keyA, keyB, valA, valB, sorted, uidx, sidx, hist, total, cnt;
-    size_t table = 0;         // filter only: the duplicate-merging hash table
-    uint64_t table_slots = 0;
-    size_t list2 = 0, rem = 0, run = 0;  // ranks only
+    size_t list2, rem, run;
     size_t total_bytes = 0;
 };
 
-PLayout layout(int64_t M, bool ranks = false) {
+PLayout layout(int64_t M) {
     PLayout L;
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -752,12 +1102,6 @@ PLayout layout(int64_t M, bool ranks = false) {
     L.passes = take(4 * 8);
     L.lo = take(8 * 8);
     L.hi = take(8 * 8);
-    L.slo = take(8 * 8);
-    L.shi = take(8 * 8);
-    L.piv = take(8 * 8 * kDirs);
-    L.pidx = take(4 * kDirs);
-    L.cscore = take(4 * kB * kCandBlocks);
-    L.cidx = take(4 * kB * kCandBlocks);
     L.flag = take(Mz);
     L.keep = take(Mz);
     L.surv = take(4 * Mz);
@@ -770,20 +1114,49 @@ PLayout layout(int64_t M, bool ranks = false) {
     L.sidx = take(4 * Mz);
     L.hist = take(4 * radix_hist_words(M));
     L.total = take(4 * 256);
-    if (!ranks) {
-        // a power of two of at least 1.5 M slots (load factor <= 2/3)
-        uint64_t c = 1024;
-        while (c < (uint64_t)Mz + Mz / 2) c <<= 1;
-        L.table_slots = c;
-        L.table = take(4 * c);
-    }
-    // per-tile counts of the compactions: over M rows, or over the table's slots
-    L.cnt = take(4 * select_cnt_words(std::max<int64_t>(M, (int64_t)L.table_slots)));
-    if (ranks) {
-        L.list2 = take(4 * Mz);
-        L.rem = take(Mz);
-        L.run = take(4 * Mz);
-    }
+    L.cnt = take(4 * select_cnt_words(M));
+    L.list2 = take(4 * Mz);
+    L.rem = take(Mz);
+    L.run = take(4 * Mz);
+    L.total_bytes = off;
+    return L;
+}
+
+// Workspace of the filter.  Counts: [0] distinct vectors, [1] left by pruning,
+// [2] left by the chunk pass, [3] the pair pass's list, [4] wide range.
+struct FLayout {
+    size_t counts = 0, lo, hi, best, bits, cnt, all, pruned, fin, dom, packed, table;
+    int64_t words = 0;  // 64-bit words of the bitmap
+    uint64_t table_slots = 0;
+    size_t total_bytes = 0;
+};
+
+FLayout filter_layout(int64_t M, int32_t m) {
+    FLayout L;
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+        size_t o = off;
+        off += align256(bytes);
+        return o;
+    };
+    const size_t Mz = (size_t)std::max<int64_t>(M, 1);
+    L.words = (int64_t)(Mz + 63) / 64;
+    L.counts = take(8 * 8);
+    L.lo = take(8 * 8);
+    L.hi = take(8 * 8);
+    L.best = take(8 * kDirs);
+    L.bits = take(8 * (size_t)L.words);
+    L.cnt = take(4 * (((size_t)Mz + kEmitTile - 1) / kEmitTile));
+    L.all = take(4 * Mz);
+    L.pruned = take(4 * Mz);
+    L.fin = take(4 * Mz);
+    L.dom = take(Mz);
+    L.packed = take(4 * Mz * (size_t)std::min(std::max(m, 1), 8));
+    // a power of two of at least 1.5 M slots (load factor <= 2/3)
+    uint64_t c = 1024;
+    while (c < (uint64_t)Mz + Mz / 2) c <<= 1;
+    L.table_slots = c;
+    L.table = take(4 * c);
     L.total_bytes = off;
     return L;
 }
@@ -794,10 +1167,8 @@ unsigned grid_for(int64_t n, int per = kB) {
 }
 
 struct PView {
-    int64_t *counts, *lo, *hi, *slo, *shi, *piv;
-    int32_t *passes, *pidx, *cidx, *surv, *valA, *valB, *sorted, *uidx, *sidx, *table;
-    uint64_t table_slots;
-    float *cscore;
+    int64_t *counts, *lo, *hi;
+    int32_t *passes, *surv, *valA, *valB, *sorted, *uidx, *sidx;
     uint8_t *flag, *keep;
     uint64_t *keyA, *keyB;
     uint32_t *hist, *total, *cnt;
@@ -810,97 +1181,127 @@ PView view(void *ws, const PLayout &L) {
     v.passes = (int32_t *)(b + L.passes);
     v.lo = (int64_t *)(b + L.lo);
     v.hi = (int64_t *)(b + L.hi);
-    v.slo = (int64_t *)(b + L.slo);
-    v.shi = (int64_t *)(b + L.shi);
-    v.piv = (int64_t *)(b + L.piv);
-    v.pidx = (int32_t *)(b + L.pidx);
-    v.cscore = (float *)(b + L.cscore);
-    v.cidx = (int32_t *)(b + L.cidx);
-    v.flag = (uint8_t *)(b + L.flag);
-    v.keep = (uint8_t *)(b + L.keep);
     v.surv = (int32_t *)(b + L.surv);
-    v.keyA = (uint64_t *)(b + L.keyA);
-    v.keyB = (uint64_t *)(b + L.keyB);
     v.valA = (int32_t *)(b + L.valA);
     v.valB = (int32_t *)(b + L.valB);
     v.sorted = (int32_t *)(b + L.sorted);
     v.uidx = (int32_t *)(b + L.uidx);
     v.sidx = (int32_t *)(b + L.sidx);
+    v.flag = (uint8_t *)(b + L.flag);
+    v.keep = (uint8_t *)(b + L.keep);
+    v.keyA = (uint64_t *)(b + L.keyA);
+    v.keyB = (uint64_t *)(b + L.keyB);
     v.hist = (uint32_t *)(b + L.hist);
     v.total = (uint32_t *)(b + L.total);
     v.cnt = (uint32_t *)(b + L.cnt);
-    v.table = L.table_slots ? (int32_t *)(b + L.table) : nullptr;
-    v.table_slots = L.table_slots;
     return v;
 }
 
-template <int MM>
-void launch_prune(const int64_t *obj, RowList rows, int64_t cap, bool pivots, const PView &v, hipStream_t st) {
-    if (pivots) {
-        const unsigned sgrid = (unsigned)std::min<int64_t>(grid_for(std::min<int64_t>(cap, kSampleRows)), 512);
-        hipLaunchKernelGGL(range_init_kernel, dim3(1), dim3(64), 0, st, v.slo, v.shi, MM);
-        hipLaunchKernelGGL(sample_range_kernel<MM>, dim3(sgrid), dim3(kB), 0, st, obj, rows, v.slo, v.shi);
-        hipLaunchKernelGGL(pivot_cand_kernel<MM>, dim3(kCandBlocks), dim3(kB), 0, st, obj, rows, v.slo, v.shi,
-                           v.cscore, v.cidx);
-        hipLaunchKernelGGL(pivot_reduce_kernel<MM>, dim3(1), dim3(kB), 0, st, obj, v.cscore, v.cidx, kCandBlocks,
-                           v.piv, v.pidx, v.counts + 3);
-    }
-    hipLaunchKernelGGL(range_init_kernel, dim3(1), dim3(64), 0, st, v.lo, v.hi, MM);
-    const unsigned grid = (unsigned)std::min<int64_t>(grid_for(cap), 4096);
-    hipLaunchKernelGGL(prune_kernel<MM>, dim3(grid), dim3(kB), 0, st, obj, rows, v.piv, v.pidx,
-                       pivots ? (const int64_t *)(v.counts + 3) : nullptr, v.flag, v.lo, v.hi);
-    QAIA_HIP(hipGetLastError());
+// list[i] = i and *count = n
+__global__ void iota_kernel(int32_t *__restrict__ list, int64_t n, int64_t *__restrict__ count) {
+    const int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x;
+    if (i == 0) *count = n;
+    if (i < n) list[i] = (int32_t)i;
 }
 
-// Prune the listed rows (or, without pivots, only take their range), compact
-// the remaining ones and sort them lexicographically descending (ties by
-// position in the list): v.sorted[0 .. counts[2]).  cap bounds the list length.
-void prune_and_sort(const int64_t *obj, RowList rows, int64_t cap, int32_t m, bool pivots, const PView &v,
-                    hipStream_t st) {
+template <int MM>
+void launch_range(const int64_t *obj, int64_t M, const PView &v, hipStream_t st) {
+    hipLaunchKernelGGL(range_init_kernel, dim3(1), dim3(64), 0, st, v.lo, v.hi, MM);
+    hipLaunchKernelGGL((sample_range_kernel<MM, false>), dim3((unsigned)std::min<int64_t>(grid_for(M), 4096)), dim3(kB),
+                       0, st, obj, RowList{nullptr, nullptr, M}, v.lo, v.hi);
+}
+
+// Sort all M rows lexicographically descending (ties by index): v.sorted[0 ..
+// M), counts[2] = M.
+void sort_rows(const int64_t *obj, int64_t M, int32_t m, const PView &v, hipStream_t st) {
     switch (m) {
-#define QAIA_PRUNE(MM) \
-    case MM: launch_prune<MM>(obj, rows, cap, pivots, v, st); break;
-        QAIA_PRUNE(1)
-        QAIA_PRUNE(2)
-        QAIA_PRUNE(3)
-        QAIA_PRUNE(4)
-        QAIA_PRUNE(5)
-        QAIA_PRUNE(6)
-        QAIA_PRUNE(7)
-        QAIA_PRUNE(8)
-#undef QAIA_PRUNE
+#define QAIA_RANGE(MM) \
+    case MM: launch_range<MM>(obj, M, v, st); break;
+        QAIA_RANGE(1)
+        QAIA_RANGE(2)
+        QAIA_RANGE(3)
+        QAIA_RANGE(4)
+        QAIA_RANGE(5)
+        QAIA_RANGE(6)
+        QAIA_RANGE(7)
+        QAIA_RANGE(8)
+#undef QAIA_RANGE
         default: throw Error{QAIA_UNSUPPORTED, "the filter supports 1..8 objectives"};
     }
     int64_t *d_S = v.counts + 2;
-    select_flagged<int32_t, int32_t>(rows.list, v.flag, rows.d_n, cap, v.surv, d_S, v.cnt, nullptr, st);
+    hipLaunchKernelGGL(iota_kernel, dim3(grid_for(M)), dim3(kB), 0, st, v.surv, M, d_S);
+    QAIA_HIP(hipGetLastError());
     for (int k = m - 1; k >= 0; --k) {
-        hipLaunchKernelGGL(sort_key_kernel, dim3(grid_for(cap)), dim3(kB), 0, st, obj, m, k, v.surv, d_S, v.lo, v.hi,
+        hipLaunchKernelGGL(sort_key_kernel, dim3(grid_for(M)), dim3(kB), 0, st, obj, m, k, v.surv, d_S, v.lo, v.hi,
                            v.keyA, v.valA, v.valB, v.passes);
         QAIA_HIP(hipGetLastError());
         for (int pass = 0; pass < 8; ++pass) {
             const bool even = (pass & 1) == 0;
             radix_pass(even ? v.keyA : v.keyB, even ? v.valA : v.valB, even ? v.keyB : v.keyA,
-                       even ? v.valB : v.valA, cap, d_S, v.passes + k, pass, v.hist, v.total, st);
+                       even ? v.valB : v.valA, M, d_S, v.passes + k, pass, v.hist, v.total, st);
         }
     }
-    hipLaunchKernelGGL(settle_kernel, dim3(grid_for(cap)), dim3(kB), 0, st, v.valA, v.valB, v.passes, d_S, v.sorted);
+    hipLaunchKernelGGL(settle_kernel, dim3(grid_for(M)), dim3(kB), 0, st, v.valA, v.valB, v.passes, d_S, v.sorted);
     QAIA_HIP(hipGetLastError());
 }
 
 template <int MM>
-void launch_dedupe(const int64_t *obj, int64_t M, const PView &v, hipStream_t st) {
-    hipLaunchKernelGGL(fill_i32_kernel, dim3(2048), dim3(kB), 0, st, v.table, (int64_t)v.table_slots, (int32_t)-1);
-    hipLaunchKernelGGL(dedupe_kernel<MM>, dim3((unsigned)std::min<int64_t>(grid_for(M, kDedupRows), 2048)), dim3(kB),
-                       0, st, obj, M, v.table, v.table_slots - 1);
+void launch_filter(const int64_t *obj, int64_t M, int64_t *keep_idx, int64_t *num_keep, char *b, const FLayout &L,
+                   hipStream_t st) {
+    int64_t *counts = (int64_t *)(b + L.counts), *lo = (int64_t *)(b + L.lo), *hi = (int64_t *)(b + L.hi);
+    unsigned long long *best = (unsigned long long *)(b + L.best);
+    uint64_t *bits = (uint64_t *)(b + L.bits);
+    uint32_t *cnt = (uint32_t *)(b + L.cnt);
+    int32_t *all = (int32_t *)(b + L.all);
+    int32_t *table = (int32_t *)(b + L.table), *pruned = (int32_t *)(b + L.pruned), *fin = (int32_t *)(b + L.fin);
+    int32_t *packed = (int32_t *)(b + L.packed);
+    uint8_t *dom = (uint8_t *)(b + L.dom);
+    const bool small = M <= kEmitSmall;
+    hipLaunchKernelGGL(filter_init_kernel, dim3((unsigned)std::min<int64_t>(grid_for((int64_t)L.table_slots / 4), 2048)),
+                       dim3(kB), 0, st, (int4 *)table, (int64_t)L.table_slots / 4, (uint32_t *)bits,
+                       small ? 0 : 2 * L.words, counts, best, lo, hi);
+    hipLaunchKernelGGL(dedupe_kernel<MM>, dim3((unsigned)std::min<int64_t>(grid_for(M, kDedupRows), 4096)), dim3(kDT),
+                       0, st, obj, M, table, (uint32_t)(L.table_slots - 1));
+    hipLaunchKernelGGL(collect_kernel, dim3((unsigned)std::min<int64_t>(grid_for((int64_t)L.table_slots, 16 * kB), kCollectBlocks)),
+                       dim3(kB), 0, st, (const int4 *)table, (int64_t)L.table_slots / 4, all, counts + 0);
+    QAIA_HIP(hipGetLastError());
+    const RowList distinct{all, counts + 0, 0};
+    // the chunk survivors reuse the distinct list's memory: by then only the pruned list is read
+    int32_t *chunked = all;
+    if (M > kPairMax) {
+        const int64_t sample = std::min<int64_t>(M, kSampleRows);
+        hipLaunchKernelGGL((sample_range_kernel<MM, true>), dim3((unsigned)std::min<int64_t>(grid_for(sample), 512)),
+                           dim3(kB), 0, st, obj, distinct, lo, hi);
+        hipLaunchKernelGGL(pivot_cand_kernel<MM>, dim3((unsigned)std::min<int64_t>(grid_for(sample), kCandBlocks)),
+                           dim3(kB), 0, st, obj, distinct, lo, hi, best);
+        hipLaunchKernelGGL(prune_kernel<MM>, dim3((unsigned)std::min<int64_t>(grid_for(M, 64), 2048)), dim3(kB), 0, st,
+                           obj, distinct, best, pruned, counts + 1);
+        hipLaunchKernelGGL(chunk_any_kernel<MM>, dim3((unsigned)std::min<int64_t>(grid_for(M, kChunk), 4096)), dim3(kB),
+                           0, st, obj, pruned, counts, chunked, counts + 2);
+    }
+    hipLaunchKernelGGL(pair_pack_kernel<MM>, dim3((unsigned)std::min<int64_t>(grid_for(M), 1024)), dim3(kB), 0, st, obj,
+                       PairList{all, pruned, chunked, counts}, counts, fin, packed, dom);
+    const int64_t tiles = grid_for(M);
+    hipLaunchKernelGGL(pair_any_kernel<MM>, dim3((unsigned)std::min<int64_t>(tiles * tiles * 8, kPairBlocks)), dim3(kB), 0,
+                       st, obj, counts, fin, packed, dom);
+    if (small) {
+        hipLaunchKernelGGL(emit_small_kernel, dim3(1), dim3(1024), 0, st, fin, dom, counts, keep_idx, num_keep);
+    } else {
+        const int64_t etiles = (M + kEmitTile - 1) / kEmitTile;
+        const bool scan = etiles > kEmitScan;
+        hipLaunchKernelGGL(mark_kernel, dim3((unsigned)std::min<int64_t>(grid_for(M), 1024)), dim3(kB), 0, st, fin, dom,
+                           counts, (uint32_t *)bits);
+        hipLaunchKernelGGL(emit_count_kernel, dim3((unsigned)etiles), dim3(kB), 0, st, bits, L.words, cnt);
+        if (scan) hipLaunchKernelGGL(emit_scan_kernel, dim3(1), dim3(kB), 0, st, cnt, etiles);
+        hipLaunchKernelGGL(emit_kernel, dim3((unsigned)etiles), dim3(kB), 0, st, bits, L.words, cnt, scan, keep_idx,
+                           num_keep);
+    }
     QAIA_HIP(hipGetLastError());
 }
 
 }  // namespace
 
-size_t pareto_ws_bytes(int64_t M, int32_t m) {
-    (void)m;
-    return layout(M).total_bytes;
-}
+size_t pareto_ws_bytes(int64_t M, int32_t m) { return filter_layout(M, m).total_bytes; }
 
 void launch_pareto(const int64_t *obj, int64_t M, int32_t m, int64_t *keep_idx, int64_t *num_keep,
                    void *ws, size_t ws_bytes, hipStream_t st) {
@@ -909,35 +1310,23 @@ void launch_pareto(const int64_t *obj, int64_t M, int32_t m, int64_t *keep_idx, 
         QAIA_HIP(hipGetLastError());
         return;
     }
-    const PLayout L = layout(M);
+    const FLayout L = filter_layout(M, m);
     QAIA_CHECK(ws_bytes >= L.total_bytes, QAIA_WORKSPACE_TOO_SMALL,
                "pareto filter workspace needs " + std::to_string(L.total_bytes) + " bytes");
-    const PView v = view(ws, L);
-    hipLaunchKernelGGL(fill_u8_kernel, dim3(grid_for(M)), dim3(kB), 0, st, v.keep, M, (uint8_t)0);
-    QAIA_HIP(hipGetLastError());
-    // 1. merge duplicates: uidx[0 .. U) = the smallest row of every distinct vector
     switch (m) {
-#define QAIA_DEDUPE(MM) \
-    case MM: launch_dedupe<MM>(obj, M, v, st); break;
-        QAIA_DEDUPE(1)
-        QAIA_DEDUPE(2)
-        QAIA_DEDUPE(3)
-        QAIA_DEDUPE(4)
-        QAIA_DEDUPE(5)
-        QAIA_DEDUPE(6)
-        QAIA_DEDUPE(7)
-        QAIA_DEDUPE(8)
-#undef QAIA_DEDUPE
+#define QAIA_FILTER(MM) \
+    case MM: launch_filter<MM>(obj, M, keep_idx, num_keep, (char *)ws, L, st); break;
+        QAIA_FILTER(1)
+        QAIA_FILTER(2)
+        QAIA_FILTER(3)
+        QAIA_FILTER(4)
+        QAIA_FILTER(5)
+        QAIA_FILTER(6)
+        QAIA_FILTER(7)
+        QAIA_FILTER(8)
+#undef QAIA_FILTER
         default: throw Error{QAIA_UNSUPPORTED, "the filter supports 1..8 objectives"};
     }
-    select_flagged<int32_t, int32_t>(v.table, nullptr, nullptr, (int64_t)v.table_slots, v.uidx, v.counts + 0, v.cnt,
-                                     nullptr, st);
-    // 2. prune the distinct vectors against the pivots and sort the rest
-    prune_and_sort(obj, RowList{v.uidx, v.counts + 0, 0}, M, m, true, v, st);
-    const int64_t *d_S = v.counts + 2;
-    // 3. the sorted survivors are distinct: chunk pass, survivor pass, ascending emission
-    nd_passes(obj, m, v.sorted, d_S, M, v.flag, v.sidx, v.counts + 1, v.cnt, v.keep, st);
-    select_flagged<int32_t, int64_t>(nullptr, v.keep, nullptr, M, keep_idx, num_keep, v.cnt, nullptr, st);
 }
 
 void launch_objective_min(const int64_t *obj, int64_t M, int32_t m, int64_t *lo, bool accumulate,
@@ -952,7 +1341,7 @@ void launch_objective_min(const int64_t *obj, int64_t M, int32_t m, int64_t *lo,
 
 size_t pareto_ranks_ws_bytes(int64_t M, int32_t m) {
     (void)m;
-    return layout(M, true).total_bytes;
+    return layout(M).total_bytes;
 }
 
 // Non-dominated sorting by peeling: sort and de-duplicate as the filter does
@@ -964,7 +1353,7 @@ size_t pareto_ranks_ws_bytes(int64_t M, int32_t m) {
 int32_t launch_pareto_ranks(const int64_t *obj, int64_t M, int32_t m, int32_t max_rank, int32_t *rank, void *ws,
                             size_t ws_bytes, hipStream_t st) {
     if (M == 0) return 0;
-    const PLayout L = layout(M, true);
+    const PLayout L = layout(M);
     QAIA_CHECK(ws_bytes >= L.total_bytes, QAIA_WORKSPACE_TOO_SMALL,
                "pareto ranks workspace needs " + std::to_string(L.total_bytes) + " bytes");
     QAIA_CHECK(M <= INT32_MAX, QAIA_INVALID_ARGUMENT, "too many rows");
@@ -974,7 +1363,7 @@ int32_t launch_pareto_ranks(const int64_t *obj, int64_t M, int32_t m, int32_t ma
     int32_t *list2 = (int32_t *)(b + L.list2), *run = (int32_t *)(b + L.run);
     hipLaunchKernelGGL(fill_u8_kernel, dim3(grid_for(M)), dim3(kB), 0, st, v.keep, M, (uint8_t)0);
     QAIA_HIP(hipGetLastError());
-    prune_and_sort(obj, RowList{nullptr, nullptr, M}, M, m, false, v, st);  // every row survives: counts[2] = M
+    sort_rows(obj, M, m, v, st);
     int32_t *cur = v.sorted;
     const int64_t *d_M = v.counts + 2;
     hipLaunchKernelGGL(unique_flag_kernel, dim3(grid_for(M)), dim3(kB), 0, st, obj, m, cur, d_M, v.flag);

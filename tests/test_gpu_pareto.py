@@ -211,3 +211,35 @@ def test_objective_min(q, M, m):
     q.qaia_objective_min(torch.from_numpy(b).cuda(), out=lo, accumulate=True)
     torch.cuda.synchronize()
     assert np.array_equal(lo.cpu().numpy(), np.minimum(want, b.min(axis=0)))
+
+
+@pytest.mark.parametrize("M", [63, 64, 65, 16384 * 3, 65535, 65536, 65537, 16384 * 5 + 1, (4096 << 14) + 1])
+def test_filter_emission_order_at_tile_edges(q, M):
+    """Ascending emission at the edges of its forms: one block up to 65536 rows,
+    tiles of 16384 rows beyond, tile counts scanned by their own launch past
+    4096 tiles.  Up to 2000 mutually non-dominated rows, among them the first
+    and the last, are planted in a pool of one repeated dominated row."""
+    import torch
+    rng = np.random.default_rng(M)
+    P = min(2000, M // 2)
+    pos = np.unique(np.concatenate([[0, M - 1], rng.integers(0, M, P)]))
+    a = rng.permutation(pos.size).astype(np.int64)
+    pool = torch.full((M, 2), -5, dtype=torch.int64, device="cuda")
+    pool[torch.from_numpy(pos).cuda()] = torch.from_numpy(np.stack([a, pos.size - a], axis=1)).cuda()
+    keep, num, _ = q.qaia_pareto_filter(pool)
+    assert np.array_equal(keep[: int(num.item())].cpu().numpy(), pos)
+
+
+@pytest.mark.parametrize("m,bits", [(1, 20), (3, 31), (3, 32), (8, 40)])
+def test_filter_long_lists_by_chunks(q, m, bits):
+    """Lists of more than 32768 distinct vectors after pruning (a front of 40 000
+    points, every second one followed by a point just below it), with ranges on
+    both sides of the 32-bit packing; and one objective, whose front is one row."""
+    rng = np.random.default_rng(m * 100 + bits)
+    a = rng.permutation(40_000).astype(np.int64) << (bits - 16)
+    cols = [a, -a] + [a * (-1) ** k + k for k in range(2, m)]
+    front = np.stack(cols[:m], axis=1)
+    lower = front[::2] - (np.arange(m) % 2 == 0)
+    pool = np.concatenate([lower, front, front[:77]])
+    want = 20_000 + np.arange(40_000) if m > 1 else np.array([20_000 + int(np.argmax(a))])
+    assert np.array_equal(_filter(q, pool), want)
