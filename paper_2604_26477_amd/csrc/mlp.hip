@@ -312,39 +312,59 @@ __global__ void front_norm_kernel(const int64_t *__restrict__ front, int64_t Pn,
 }
 
 // per front point: distance to the nearest other point and the fraction of
-// points within 0.05 (itself included); the front passes through LDS in
-// chunks shared by the block
-constexpr int kLChunk = 2048;
+// points within 0.05 (itself included).  A block takes 64 points j, one per
+// lane, and each of its sixteen waves a sixteenth of the points i, read at
+// uniform addresses (scalar loads).  Squared distances are compared: the square
+// root is monotone and correctly rounded, so sqrt(min d2) = min sqrt(d2), and
+// sqrt(d2) <= 0.05f exactly when d2 <= kNear2, the largest float whose root is.
+// Bound by the latency of the sixteenth's chain; 2048 points of four
+// objectives: 866 us with a thread per j (8 blocks) and a root per pair, now 16.
+constexpr float kNear2 = 0x1.47ae16p-9f;
+constexpr int kLWaves = 16;
 
-__global__ __launch_bounds__(kB) void front_local_kernel(const float *__restrict__ yh, int64_t Pn, int m,
-                                                         float *__restrict__ nn, float *__restrict__ frac) {
-    __shared__ float stage[kLChunk * 8];
-    const int64_t j = (int64_t)blockIdx.x * kB + threadIdx.x;
+template <int M>
+__global__ __launch_bounds__(64 * kLWaves) void front_local_kernel(const float *__restrict__ yh, int64_t Pn,
+                                                                   float *__restrict__ nn, float *__restrict__ frac) {
+    __shared__ float best_sh[kLWaves][64];
+    __shared__ int32_t close_sh[kLWaves][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t j0 = (int64_t)blockIdx.x * 64, j = j0 + lane;
     const bool active = j < Pn;
-    float me[8];
-    for (int k = 0; k < m; ++k) me[k] = active ? yh[j * m + k] : 0.0f;
+    float me[M];
+#pragma unroll
+    for (int k = 0; k < M; ++k) me[k] = active ? yh[j * M + k] : 0.0f;
     float best = INFINITY;
-    int64_t close = 0;
-    for (int64_t base = 0; base < Pn; base += kLChunk) {
-        const int cnt = (int)(Pn - base < kLChunk ? Pn - base : kLChunk);
-        __syncthreads();
-        for (int i = threadIdx.x; i < cnt * m; i += kB) stage[i] = yh[base * m + i];
-        __syncthreads();
-        if (active)
-            for (int i = 0; i < cnt; ++i) {
-                float d2 = 0.0f;
-                for (int k = 0; k < m; ++k) {
-                    const float d = stage[i * m + k] - me[k];
-                    d2 = fmaf(d, d, d2);
-                }
-                const float d = sqrtf(d2);
-                if (base + i != j && d < best) best = d;
-                if (d <= 0.05f) ++close;
-            }
+    int32_t close = 0;
+    const int64_t per = (Pn + kLWaves - 1) / kLWaves;
+    const int64_t i0 = min(Pn, wave * per), i1 = min(Pn, i0 + per);
+    auto visit = [&](int64_t i, bool other) __attribute__((always_inline)) {
+        float d2 = 0.0f;
+#pragma unroll
+        for (int k = 0; k < M; ++k) {
+            const float d = yh[i * M + k] - me[k];
+            d2 = fmaf(d, d, d2);
+        }
+        close += d2 <= kNear2 ? 1 : 0;
+        best = fminf(best, other ? d2 : INFINITY);
+    };
+    // the block's own points need the test for the point itself
+    const int64_t a = min(i1, max(i0, j0)), b = min(i1, max(i0, j0 + 64));
+#pragma unroll 4
+    for (int64_t i = i0; i < a; ++i) visit(i, true);
+    for (int64_t i = a; i < b; ++i) visit(i, i != j);
+#pragma unroll 4
+    for (int64_t i = b; i < i1; ++i) visit(i, true);
+    best_sh[wave][lane] = best;
+    close_sh[wave][lane] = close;
+    __syncthreads();
+    if (wave != 0 || !active) return;
+    int64_t n = 0;
+    for (int w = 0; w < kLWaves; ++w) {
+        best = fminf(best, best_sh[w][lane]);
+        n += close_sh[w][lane];
     }
-    if (!active) return;
-    nn[j] = Pn > 1 ? best : 0.0f;
-    frac[j] = (float)close / (float)Pn;
+    nn[j] = Pn > 1 ? sqrtf(best) : 0.0f;
+    frac[j] = (float)n / (float)Pn;
 }
 
 template <int M>
@@ -368,16 +388,32 @@ __device__ float angle(const float (&a)[M], const float *b) {
     return 2.0f * atan2f(sqrtf(dm), sqrtf(dp));
 }
 
-// one thread per candidate weight vector; the front and the last round's hit
-// and miss vectors are staged through LDS in chunks shared by the block.  The
+// A block takes 64 candidate weight vectors, one per lane; the front and the
+// last round's hit and miss vectors are staged through LDS in chunks, and each
+// of the four waves walks a quarter of every chunk, so that 65 536 candidates
+// put four waves on every SIMD.  The waves' results are merged at the end.  The
 // smallest angle to a set is taken at the set member with the largest cosine
 // (the angle decreases with the cosine) and then evaluated accurately once.
+// Ties go to the smallest index throughout, as in one pass over the set.  ALU
+// bound: M + 12 instructions per front point (M products, eight for the sorted
+// list of the largest values: with top[i-1] >= top[i], inserting v makes
+// top[i] the median of the three; two for the
+// maximiser, one against NaN).  65 536 candidates,
+// 2048 points: 367 us with a thread per candidate and an insertion loop, now 88.
 constexpr int kFChunk = 1024;
+constexpr int kFWaves = kB / 64;
+
+// this wave's quarter [i0, i1) of a chunk of cnt members
+__device__ __forceinline__ void quarter(int cnt, int wave, int &i0, int &i1) {
+    const int per = (cnt + kFWaves - 1) / kFWaves;
+    i0 = min(cnt, wave * per);
+    i1 = min(cnt, i0 + per);
+}
 
 template <int M>
 __device__ __forceinline__ void best_cosine(const float (&u)[M], const float *__restrict__ vecs, int64_t count,
-                                            float *stage, bool active, int64_t &best) {
-    float bc = -INFINITY;
+                                            float *stage, int wave, float &bc, int64_t &best) {
+    bc = -INFINITY;
     best = -1;
     for (int64_t base = 0; base < count; base += kFChunk) {
         const int cnt = (int)(count - base < kFChunk ? count - base : kFChunk);
@@ -391,16 +427,18 @@ __device__ __forceinline__ void best_cosine(const float (&u)[M], const float *__
             for (int k = 0; k < M; ++k) stage[i * M + k] = vecs[(base + i) * M + k] * inv;
         }
         __syncthreads();
-        if (active)
-            for (int i = 0; i < cnt; ++i) {
-                float d = 0.0f;
+        int i0, i1;
+        quarter(cnt, wave, i0, i1);
+        int at = -1;
+#pragma unroll 4
+        for (int i = i0; i < i1; ++i) {
+            float d = 0.0f;
 #pragma unroll
-                for (int k = 0; k < M; ++k) d = fmaf(u[k], stage[i * M + k], d);
-                if (d > bc) {
-                    bc = d;
-                    best = base + i;
-                }
-            }
+            for (int k = 0; k < M; ++k) d = fmaf(u[k], stage[i * M + k], d);
+            at = d > bc ? i : at;
+            bc = d > bc ? d : bc;
+        }
+        if (at >= 0) best = base + at;
     }
 }
 
@@ -411,8 +449,11 @@ __global__ __launch_bounds__(kB) void features_kernel(const float *__restrict__ 
                                                       const float *__restrict__ hits, int64_t Hn,
                                                       const float *__restrict__ misses, int64_t Mn,
                                                       float *__restrict__ feat) {
-    __shared__ float stage[kFChunk * M];
-    const int64_t c = (int64_t)blockIdx.x * kB + threadIdx.x;
+    __shared__ __attribute__((aligned(16))) float stage[kFChunk * M];
+    __shared__ float top_sh[kFWaves][8][64], cos_sh[kFWaves][2][64];
+    __shared__ int64_t at_sh[kFWaves][3][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t c = (int64_t)blockIdx.x * 64 + lane;
     const bool active = c < N;
     float w[M], u[M];
     float nw = 0.0f;
@@ -424,44 +465,74 @@ __global__ __launch_bounds__(kB) void features_kernel(const float *__restrict__ 
     const float inv = nw > 0.0f ? 1.0f / sqrtf(nw) : 0.0f;
 #pragma unroll
     for (int k = 0; k < M; ++k) u[k] = w[k] * inv;
-    float f[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     // max, second and eighth largest of v_j = c . yh_j over the front, and the maximiser
     float top[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) top[i] = -INFINITY;
     int64_t jstar = 0;
+    // (a product that is no number, from weights that are none, is left out)
+    auto insert = [&](float v) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 7; i > 0; --i) top[i] = __builtin_amdgcn_fmed3f(top[i - 1], v, top[i]);
+        top[0] = fmaxf(top[0], v);
+    };
     for (int64_t base = 0; base < Pn; base += kFChunk) {
         const int cnt = (int)(Pn - base < kFChunk ? Pn - base : kFChunk);
         __syncthreads();
         for (int i = threadIdx.x; i < cnt * M; i += kB) stage[i] = yh[base * M + i];
         __syncthreads();
-        if (active)
-            for (int jj = 0; jj < cnt; ++jj) {
-                float v = 0.0f;
+        int i0, i1;
+        quarter(cnt, wave, i0, i1);
+        int at = -1;
+#pragma unroll 4
+        for (int jj = i0; jj < i1; ++jj) {
+            float v = 0.0f;
 #pragma unroll
-                for (int k = 0; k < M; ++k) v = fmaf(w[k], stage[jj * M + k], v);
-                if (v > top[0]) jstar = base + jj;  // first index on ties
-                if (v > top[7]) {
-                    int i = 7;
-                    while (i > 0 && top[i - 1] < v) {
-                        top[i] = top[i - 1];
-                        --i;
-                    }
-                    top[i] = v;
-                }
-            }
+            for (int k = 0; k < M; ++k) v = fmaf(w[k], stage[jj * M + k], v);
+            at = v > top[0] ? jj : at;  // first index on ties
+            insert(fmaxf(v, -INFINITY));
+        }
+        if (at >= 0) jstar = base + at;
     }
+    float hc, mc;
+    int64_t bh, bm;
+    best_cosine<M>(u, hits, Hn, stage, wave, hc, bh);
+    best_cosine<M>(u, misses, Mn, stage, wave, mc, bm);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) top_sh[wave][i][lane] = top[i];
+    cos_sh[wave][0][lane] = hc;
+    cos_sh[wave][1][lane] = mc;
+    at_sh[wave][0][lane] = jstar;
+    at_sh[wave][1][lane] = bh;
+    at_sh[wave][2][lane] = bm;
+    __syncthreads();
+    if (wave != 0 || !active) return;
+    // a wave's larger value, or its equal value at a smaller index, replaces the best so far
+    auto better = [](float v, int64_t at, float &best, int64_t &best_at) {
+        if (at >= 0 && (best_at < 0 || v > best || (v == best && at < best_at))) {
+            best = v;
+            best_at = at;
+        }
+    };
+    for (int o = 1; o < kFWaves; ++o) {
+        float t0 = top[0];
+        if (top_sh[o][0][lane] > -INFINITY) better(top_sh[o][0][lane], at_sh[o][0][lane], t0, jstar);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) insert(top_sh[o][i][lane]);
+        better(cos_sh[o][0][lane], at_sh[o][1][lane], hc, bh);
+        better(cos_sh[o][1][lane], at_sh[o][2][lane], mc, bm);
+    }
+    float f[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if (Pn > 0) {
         f[0] = top[0];
         f[1] = Pn > 1 ? top[0] - top[1] : 0.0f;
-        f[2] = top[0] - top[Pn < 8 ? Pn - 1 : 7];
+        float last = top[0];
+#pragma unroll
+        for (int i = 1; i < 8; ++i) last = i < Pn ? top[i] : last;
+        f[2] = top[0] - last;
         f[3] = nn[jstar];
         f[4] = frac[jstar];
     }
-    int64_t bh, bm;
-    best_cosine<M>(u, hits, Hn, stage, active, bh);
-    best_cosine<M>(u, misses, Mn, stage, active, bm);
-    if (!active) return;
     f[5] = bh >= 0 ? angle<M>(w, hits + bh * M) : 1.57079632679489662f;
     f[6] = bm >= 0 ? angle<M>(w, misses + bm * M) : 1.57079632679489662f;
     float dev = 0.0f;
@@ -692,11 +763,13 @@ void launch_features(const int64_t *front, int64_t Pn, int m, const float *cands
     if (Pn > 0) {
         hipLaunchKernelGGL(front_range_kernel, dim3(1), dim3(kB), 0, st, front, Pn, m, lohi);
         hipLaunchKernelGGL(front_norm_kernel, dim3(blocks_for(Pn * m)), dim3(kB), 0, st, front, Pn, m, lohi, yh);
-        hipLaunchKernelGGL(front_local_kernel, dim3(blocks_for(Pn)), dim3(kB), 0, st, yh, Pn, m, nn, frac);
     }
 #define QAIA_FEATURES(MM)                                                                                     \
     case MM:                                                                                                  \
-        hipLaunchKernelGGL(features_kernel<MM>, dim3(blocks_for(N)), dim3(kB), 0, st, yh, Pn, nn, frac, cands, N, \
+        if (Pn > 0)                                                                                           \
+            hipLaunchKernelGGL(front_local_kernel<MM>, dim3((unsigned)((Pn + 63) / 64)), dim3(64 * kLWaves), 0, st, yh, \
+                               Pn, nn, frac);                                                                 \
+        hipLaunchKernelGGL(features_kernel<MM>, dim3((unsigned)((N + 63) / 64)), dim3(kB), 0, st, yh, Pn, nn, frac, cands, N, \
                            hits, Hn, misses, Mn, feat);                                                       \
         break;
     switch (m) {

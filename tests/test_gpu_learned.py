@@ -176,6 +176,21 @@ def test_features_match_oracle(q):
     np.testing.assert_allclose(got0[:, m:], want0, rtol=0, atol=2e-6)
 
 
+@pytest.mark.parametrize("m,P,N,H,Mn", [(1, 1, 1, 1, 0), (2, 7, 63, 0, 1), (3, 8, 64, 3, 5), (4, 9, 65, 1023, 1025),
+                                        (8, 1025, 300, 2, 3), (5, 2049, 129, 0, 0)])
+def test_features_at_tile_edges(q, m, P, N, H, Mn):
+    """Fronts, candidates and hit / miss sets on both sides of the 64-candidate
+    block, the quarters and the 1024-member chunks.  Tolerances as above: the
+    features are differences of unit-range float32 values."""
+    rng = np.random.default_rng(100 * m + P)
+    front = rng.integers(-10**6, 10**7, size=(P, m)).astype(np.int64)
+    cands, hits, misses = (rng.dirichlet(np.ones(m), size=k).astype(np.float32).reshape(k, m) for k in (N, H, Mn))
+    got = q.qaia_front_features(_dev(front), _dev(cands), _dev(hits), _dev(misses)).cpu().numpy()
+    want = omlp.features(front, cands.astype(np.float64), hits.astype(np.float64), misses.astype(np.float64))
+    np.testing.assert_array_equal(got[:, :m], cands)
+    np.testing.assert_allclose(got[:, m:], want, rtol=0, atol=2e-5)
+
+
 def test_topk_gather_and_labels(q):
     import torch
     rng = np.random.default_rng(7)
