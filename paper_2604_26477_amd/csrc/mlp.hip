@@ -552,34 +552,289 @@ __global__ __launch_bounds__(kB) void features_kernel(const float *__restrict__ 
 // Gumbel-perturbed keys: the top k of score / tau + G (G standard Gumbel from
 // the counter stream) is a sample of k items without replacement with
 // probabilities proportional to exp(score / tau).
-__global__ void gumbel_keys_kernel(const float *__restrict__ scores, int64_t N, float inv_tau, uint64_t seed,
-                                   float *__restrict__ keys) {
-    const int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x;
-    if (i >= N) return;
+__device__ __forceinline__ float gumbel_key(float score, float inv_tau, uint64_t seed, int64_t i) {
     uint64_t z = seed + ((uint64_t)i + 1ull) * 0x9e3779b97f4a7c15ull;
     z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
     z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
     z ^= z >> 31;
     const float u = ((float)(uint32_t)(z >> 40) + 0.5f) * 0x1p-24f;  // (0, 1)
-    keys[i] = scores[i] * inv_tau - logf(-logf(u));
+    return score * inv_tau - logf(-logf(u));
 }
 
-// Sort keys of the top-k selection: descending score order as an ascending
-// unsigned key (the IEEE bit pattern made monotone, then complemented; -0 is
-// taken as +0), value = item index.  Block 0 also stores the item and digit
-// pass counts the sort reads from device memory.
-__global__ void topk_key_kernel(const float *__restrict__ s, int64_t N, uint64_t *__restrict__ key,
-                                int32_t *__restrict__ val, int64_t *__restrict__ d_n, int32_t *__restrict__ d_passes) {
+// The key as an unsigned number in the order of the scores (the IEEE bit
+// pattern made monotone; -0 is taken as +0).
+__device__ __forceinline__ uint32_t key_bits(float f) {
+    const uint32_t b = f == 0.0f ? 0u : __float_as_uint(f);
+    return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+}
+
+// The key bits alone, for the ranks over all items.
+__global__ void topk_bits_kernel(const float *__restrict__ s, int64_t N, bool gumbel, float inv_tau, uint64_t seed,
+                                 uint32_t *__restrict__ key) {
+    const int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x;
+    if (i < N) key[i] = key_bits(gumbel ? gumbel_key(s[i], inv_tau, seed, i) : s[i]);
+}
+
+// comp[i] = (key bits, ~i): distinct, and larger is earlier in the result.
+// Also clears `words` words that the following launches count in.
+__global__ void topk_comp_kernel(const float *__restrict__ s, int64_t N, bool gumbel, float inv_tau, uint64_t seed,
+                                 uint64_t *__restrict__ comp, uint32_t *__restrict__ clear, int words) {
+    const int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x;
+    if (blockIdx.x == 0)
+        for (int w = threadIdx.x; w < words; w += kB) clear[w] = 0u;
+    if (i >= N) return;
+    const float f = gumbel ? gumbel_key(s[i], inv_tau, seed, i) : s[i];
+    comp[i] = ((uint64_t)key_bits(f) << 32) | (uint32_t)~(uint32_t)i;
+}
+
+// One block's 64 items of a list (block b: items 64 b ..), one per lane, ranked
+// against the n items of the list, a sixteenth per wave at uniform addresses:
+// out[rank] = item for rank < k.  Two instructions per pair.
+constexpr int kRankWaves = 16;
+__device__ __forceinline__ void rank_block(const uint64_t *__restrict__ comp, int64_t n, int64_t k, int64_t b,
+                                           int64_t *__restrict__ out, int32_t *sh) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t i = b * 64 + lane;
+    const uint64_t mine = i < n ? comp[i] : 0ull;
+    const int64_t per = ((n + kRankWaves - 1) / kRankWaves + 7) & ~int64_t(7);
+    const int64_t j0 = min(n, wave * per), j1 = min(n, j0 + per);
+    int32_t r = 0;
+#pragma unroll 8
+    for (int64_t j = j0; j < j1; ++j) r += comp[j] > mine ? 1 : 0;
+    sh[wave * 64 + lane] = r;
+    __syncthreads();
+    if (wave != 0 || i >= n) return;
+    int64_t rank = 0;
+    for (int w = 0; w < kRankWaves; ++w) rank += sh[w * 64 + lane];
+    if (rank < k) out[rank] = (int64_t)(uint32_t)~(uint32_t)mine;
+}
+
+// Every item's rank among n <= kRankAll, on the 32-bit keys in index order.  A
+// block stages all keys in LDS and ranks 32 items; its 32 half-waves take a
+// slice of the keys each, four per LDS read (the same address for the half).
+// Equal keys rank by index: items before the block's own count when >=, items
+// after it when >.
+constexpr int kRankItems = 32;
+constexpr int64_t kRankAll = 12288;  // 48 KB of keys
+__global__ __launch_bounds__(64 * kRankWaves) void topk_rank_kernel(const uint32_t *__restrict__ key, int n, int64_t k,
+                                                                    int64_t *__restrict__ out) {
+    extern __shared__ __attribute__((aligned(16))) uint32_t keys[];  // n rounded up to 4, zero padded
+    __shared__ int32_t sh[2 * kRankWaves][kRankItems];
+    const int n4 = (n + 3) & ~3;
+#pragma unroll 4
+    for (int j = 4 * threadIdx.x; j < n4; j += 4 * 64 * kRankWaves) {
+        uint4 q = *(const uint4 *)(key + j);  // (the key buffer has room for a multiple of 4)
+        q.y = j + 1 < n ? q.y : 0u;
+        q.z = j + 2 < n ? q.z : 0u;
+        q.w = j + 3 < n ? q.w : 0u;
+        *(uint4 *)(keys + j) = q;
+    }
+    __syncthreads();
+    const int item = threadIdx.x & (kRankItems - 1), slice = threadIdx.x / kRankItems;
+    const int b0 = (int)blockIdx.x * kRankItems, i = b0 + item;
+    const uint32_t mine = i < n ? keys[i] : 0u;
+    const int per = ((n4 + 2 * kRankWaves - 1) / (2 * kRankWaves) + 3) & ~3;
+    const int j0 = min(n4, slice * per), j1 = min(n4, j0 + per);
+    const int a = min(j1, max(j0, b0)), b = min(j1, max(j0, b0 + kRankItems));  // all multiples of 4
+    int32_t r = 0;
+#pragma unroll 4
+    for (int j = j0; j < a; j += 4) {
+        const uint4 q = *(const uint4 *)(keys + j);
+        r += (q.x >= mine) + (q.y >= mine) + (q.z >= mine) + (q.w >= mine);
+    }
+    for (int j = a; j < b; ++j) r += keys[j] > mine || (keys[j] == mine && j < i) ? 1 : 0;
+#pragma unroll 4
+    for (int j = b; j < j1; j += 4) {
+        const uint4 q = *(const uint4 *)(keys + j);
+        r += (q.x > mine) + (q.y > mine) + (q.z > mine) + (q.w > mine);
+    }
+    sh[slice][item] = r;
+    __syncthreads();
+    if (threadIdx.x >= kRankItems || i >= n) return;
+    int64_t rank = 0;
+#pragma unroll
+    for (int w = 0; w < 2 * kRankWaves; ++w) rank += sh[w][item];
+    if (rank < k) out[rank] = i;
+}
+
+// Selection for few of many: the key bits of the k-th item are found by three
+// histograms (11, 11 and 10 bits), the items above it (fewer than k) are listed
+// and ranked, and of the items equal to it the first by index fill the rest.
+constexpr int kSelBins = 2048;
+struct SelState {
+    uint32_t bin[3], above[3];  // per level: the k-th item's bin, and the items in higher bins
+    uint32_t listed;            // items appended to the list
+    uint32_t pad;
+};
+constexpr int kSelMaxK = 4096;    // longest list to rank by pairs
+constexpr int kSelChunks = 1024;  // blocks of the passes over the items (at most)
+
+// Block-wide (256 threads): the bin of the k-th largest item (k >= 1, at most
+// the items counted) and how many are in higher bins.
+__device__ __forceinline__ void find_bin(const uint32_t *__restrict__ hist, uint32_t k, uint32_t &bin, uint32_t &above,
+                                         uint32_t *sh) {
+    constexpr int PER = kSelBins / kB;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t c[PER], sum = 0;  // this thread's bins, from the top: kSelBins - 1 - (PER t + q)
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        c[q] = hist[kSelBins - 1 - (PER * (int)threadIdx.x + q)];
+        sum += c[q];
+    }
+    uint32_t s = sum;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t o = __shfl_up(s, off);
+        if (lane >= off) s += o;
+    }
+    if (lane == 63) sh[wave] = s;
+    __syncthreads();
+    uint32_t before = s - sum;
+    for (int w = 0; w < wave; ++w) before += sh[w];
+    if (before < k && k <= before + sum) {
+        uint32_t run = before;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            if (run < k && k <= run + c[q]) {
+                sh[4] = kSelBins - 1 - (PER * threadIdx.x + q);
+                sh[5] = run;
+            }
+            run += c[q];
+        }
+    }
+    __syncthreads();
+    bin = sh[4];
+    above = sh[5];
+    __syncthreads();
+}
+
+template <int LEVEL>
+__global__ __launch_bounds__(kB) void topk_hist_kernel(const uint64_t *__restrict__ comp, int64_t N, int64_t chunk,
+                                                       uint32_t k, uint32_t *__restrict__ hist, SelState *st) {
+    __shared__ uint32_t h[kSelBins];
+    __shared__ uint32_t sh[8];
+    uint32_t prefix = 0;
+    if constexpr (LEVEL > 0) {
+        uint32_t bin, above;
+        find_bin(hist + (LEVEL - 1) * kSelBins, LEVEL == 1 ? k : k - st->above[0], bin, above, sh);
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            st->bin[LEVEL - 1] = bin;
+            st->above[LEVEL - 1] = above;
+        }
+        prefix = LEVEL == 1 ? bin : (st->bin[0] << 11) | bin;
+    }
+    for (int i = threadIdx.x; i < kSelBins; i += kB) h[i] = 0u;
+    __syncthreads();
+    const int64_t i0 = (int64_t)blockIdx.x * chunk, i1 = min(N, i0 + chunk);
+    for (int64_t i = i0 + threadIdx.x; i < i1; i += kB) {
+        const uint32_t u = (uint32_t)(comp[i] >> 32);
+        if (LEVEL == 0) atomicAdd(&h[u >> 21], 1u);
+        if (LEVEL == 1 && (u >> 21) == prefix) atomicAdd(&h[(u >> 10) & 2047u], 1u);
+        if (LEVEL == 2 && (u >> 10) == prefix) atomicAdd(&h[u & 1023u], 1u);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < kSelBins; i += kB)
+        if (h[i]) atomicAdd(&hist[LEVEL * kSelBins + i], h[i]);
+}
+
+// list[0 ..) = the items above the k-th key; equal[block] = the block's items at it.
+__global__ __launch_bounds__(kB) void topk_collect_kernel(const uint64_t *__restrict__ comp, int64_t N, int64_t chunk,
+                                                          uint32_t k, const uint32_t *__restrict__ hist, SelState *st,
+                                                          uint64_t *__restrict__ list, uint32_t *__restrict__ equal) {
+    __shared__ uint32_t sh[8];
+    __shared__ uint32_t eq;
+    if (threadIdx.x == 0) eq = 0u;
+    uint32_t bin, above;
+    find_bin(hist + 2 * kSelBins, k - st->above[0] - st->above[1], bin, above, sh);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        st->bin[2] = bin;
+        st->above[2] = above;
+    }
+    const uint32_t key = (st->bin[0] << 21) | (st->bin[1] << 10) | bin;
+    const int64_t i0 = (int64_t)blockIdx.x * chunk, i1 = min(N, i0 + chunk);
+    for (int64_t c0 = i0; c0 < i1; c0 += 4 * kB) {  // one global atomic per 1024 items
+        uint64_t c[4];
+        uint32_t at[4];
+        if (threadIdx.x == 0) sh[6] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int64_t i = c0 + r * kB + threadIdx.x;
+            c[r] = i < i1 ? comp[i] : 0ull;
+            const uint32_t u = (uint32_t)(c[r] >> 32);
+            at[r] = i < i1 && u > key ? atomicAdd(&sh[6], 1u) : ~0u;
+            if (i < i1 && u == key) atomicAdd(&eq, 1u);
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) sh[7] = sh[6] ? atomicAdd(&st->listed, sh[6]) : 0u;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (at[r] != ~0u) list[sh[7] + at[r]] = c[r];
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) equal[blockIdx.x] = eq;
+}
+
+// Blocks [0, rank_blocks): the listed items in order.  The others, one per
+// chunk: the chunk's items at the k-th key, in index order, after them.
+__global__ __launch_bounds__(64 * kRankWaves) void topk_emit_kernel(const uint64_t *__restrict__ comp, int64_t N,
+                                                                    int64_t chunk, int64_t k, int rank_blocks,
+                                                                    const SelState *__restrict__ st,
+                                                                    const uint64_t *__restrict__ list,
+                                                                    const uint32_t *__restrict__ equal,
+                                                                    int64_t *__restrict__ out) {
+    __shared__ int32_t sh[kRankWaves * 64];
+    const int64_t above = (int64_t)st->above[0] + st->above[1] + st->above[2];
+    if ((int)blockIdx.x < rank_blocks) {
+        if ((int64_t)blockIdx.x * 64 < above) rank_block(list, above, k, blockIdx.x, out, sh);
+        return;
+    }
+    const int b = (int)blockIdx.x - rank_blocks, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (equal[b] == 0) return;
+    auto total = [&](int v) {
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+        if (lane == 0) sh[wave] = v;
+        __syncthreads();
+        int s = 0;
+        for (int w = 0; w < kRankWaves; ++w) s += sh[w];
+        __syncthreads();
+        return s;
+    };
+    const int before = total((int)threadIdx.x < b ? (int)equal[threadIdx.x] : 0);  // at most 1024 chunks
+    const uint32_t key = (st->bin[0] << 21) | (st->bin[1] << 10) | st->bin[2];
+    int64_t at = above + before;
+    const int64_t i0 = (int64_t)b * chunk, i1 = min(N, i0 + chunk);
+    for (int64_t i = i0 + threadIdx.x; i - (int64_t)threadIdx.x < i1 && at < k; i += 64 * kRankWaves) {
+        const bool mine = i < i1 && (uint32_t)(comp[i] >> 32) == key;
+        const uint64_t mask = __ballot(mine);
+        if (lane == 0) sh[wave] = __popcll(mask);
+        __syncthreads();
+        int pre = 0, all = 0;
+        for (int w = 0; w < kRankWaves; ++w) {
+            if (w < wave) pre += sh[w];
+            all += sh[w];
+        }
+        const int64_t pos = at + pre + __popcll(mask & ((1ull << lane) - 1ull));
+        if (mine && pos < k) out[pos] = i;
+        at += all;
+        __syncthreads();
+    }
+}
+
+// The radix sort's keys: ascending unsigned order is descending score order.
+// Block 0 also stores the item and digit pass counts that the sort reads from
+// device memory.
+__global__ void topk_key_kernel(const float *__restrict__ s, int64_t N, bool gumbel, float inv_tau, uint64_t seed,
+                                uint64_t *__restrict__ key, int32_t *__restrict__ val, int64_t *__restrict__ d_n,
+                                int32_t *__restrict__ d_passes) {
     const int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x;
     if (i == 0) {
         *d_n = N;
         *d_passes = 4;
     }
     if (i >= N) return;
-    const float f = s[i];
-    uint32_t b = f == 0.0f ? 0u : __float_as_uint(f);
-    b = (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-    key[i] = (uint64_t)(~b);
+    const float f = gumbel ? gumbel_key(s[i], inv_tau, seed, i) : s[i];
+    key[i] = (uint64_t)(uint32_t)~key_bits(f);
     val[i] = (int32_t)i;
 }
 
@@ -789,10 +1044,18 @@ void launch_features(const int64_t *front, int64_t Pn, int m, const float *cands
 
 size_t topk_ws_bytes(int64_t N) {
     const size_t n = (size_t)std::max<int64_t>(N, 1);
-    return align256(sizeof(float) * n) + 2 * align256(sizeof(uint64_t) * n) + 2 * align256(sizeof(int32_t) * n) +
-           align256(4 * radix_hist_words(N)) + align256(4 * 256) + align256(64);
+    return 2 * align256(sizeof(uint64_t) * n) + 2 * align256(sizeof(int32_t) * n) + align256(4 * radix_hist_words(N)) +
+           align256(4 * 256) + align256(64);
 }
 
+// Three ways to the same order, by size:
+//  - up to kRankAll items: every item's rank by comparing all pairs, two
+//    launches (8192 items, all returned: 17 us; the radix sort's fourteen
+//    launches took 120 us at 8192 items and 134 at 65 536; past 12 288 items
+//    the pairs take as long as the selection);
+//  - more items, at most kSelMaxK returned: selection, six launches (65 536
+//    items, 922 returned: 28 us);
+//  - otherwise the stable radix sort.
 void launch_topk(const float *scores, int64_t N, int64_t k, float temperature, uint64_t seed, int64_t *idx_out,
                  void *ws, size_t ws_bytes, hipStream_t st) {
     QAIA_CHECK(N >= 1 && N < (int64_t(1) << 31), QAIA_INVALID_ARGUMENT, "N must be in [1, 2^31)");
@@ -800,6 +1063,7 @@ void launch_topk(const float *scores, int64_t N, int64_t k, float temperature, u
     QAIA_CHECK(ws_bytes >= topk_ws_bytes(N), QAIA_WORKSPACE_TOO_SMALL, "top-k workspace too small");
     QAIA_CHECK(temperature >= 0.0f && std::isfinite(temperature), QAIA_INVALID_ARGUMENT,
                "temperature must be finite and >= 0");
+    if (k == 0) return;
     char *b = (char *)ws;
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -807,31 +1071,55 @@ void launch_topk(const float *scores, int64_t N, int64_t k, float temperature, u
         off += align256(bytes);
         return p;
     };
-    float *pert = (float *)take(sizeof(float) * (size_t)N);
     uint64_t *keyA = (uint64_t *)take(sizeof(uint64_t) * (size_t)N), *keyB = (uint64_t *)take(sizeof(uint64_t) * (size_t)N);
     int32_t *valA = (int32_t *)take(sizeof(int32_t) * (size_t)N), *valB = (int32_t *)take(sizeof(int32_t) * (size_t)N);
     uint32_t *hist = (uint32_t *)take(4 * radix_hist_words(N)), *total = (uint32_t *)take(4 * 256);
     char *small = take(64);
+    const bool gumbel = temperature > 0.0f;
+    const float inv_tau = gumbel ? 1.0f / temperature : 0.0f;
+    const dim3 items(blocks_for(N)), block(kB), rank_block(64 * kRankWaves);
+    if (N <= kRankAll) {
+        uint32_t *bits = (uint32_t *)keyA;
+        hipLaunchKernelGGL(topk_bits_kernel, items, block, 0, st, scores, N, gumbel, inv_tau, seed, bits);
+        hipLaunchKernelGGL(topk_rank_kernel, dim3((unsigned)((N + kRankItems - 1) / kRankItems)), rank_block,
+                           4 * (size_t)((N + 3) & ~int64_t(3)), st, bits, (int)N, k, idx_out);
+        QAIA_HIP(hipGetLastError());
+        return;
+    }
+    if (k <= kSelMaxK) {
+        // in keyB's memory (8 N > 131 072 bytes): the list, the histograms, the state, the chunks' counts
+        uint64_t *list = keyB;
+        uint32_t *bins = (uint32_t *)(list + kSelMaxK);
+        SelState *state = (SelState *)(bins + 3 * kSelBins);
+        uint32_t *equal = (uint32_t *)(state + 1);
+        static_assert(8 * kSelMaxK + 12 * kSelBins + sizeof(SelState) + 4 * kSelChunks <= 8 * (size_t)kRankAll, "fits");
+        const int64_t chunk = ((N + kSelChunks - 1) / kSelChunks + 1023) / 1024 * 1024;
+        const unsigned chunks = (unsigned)((N + chunk - 1) / chunk);
+        const int rank_blocks = (int)((k + 63) / 64);
+        hipLaunchKernelGGL(topk_comp_kernel, items, block, 0, st, scores, N, gumbel, inv_tau, seed, keyA, bins,
+                           3 * kSelBins + (int)(sizeof(SelState) / 4));
+        hipLaunchKernelGGL(topk_hist_kernel<0>, dim3(chunks), block, 0, st, keyA, N, chunk, (uint32_t)k, bins, state);
+        hipLaunchKernelGGL(topk_hist_kernel<1>, dim3(chunks), block, 0, st, keyA, N, chunk, (uint32_t)k, bins, state);
+        hipLaunchKernelGGL(topk_hist_kernel<2>, dim3(chunks), block, 0, st, keyA, N, chunk, (uint32_t)k, bins, state);
+        hipLaunchKernelGGL(topk_collect_kernel, dim3(chunks), block, 0, st, keyA, N, chunk, (uint32_t)k, bins, state, list,
+                           equal);
+        hipLaunchKernelGGL(topk_emit_kernel, dim3(rank_blocks + chunks), rank_block, 0, st, keyA, N, chunk, k, rank_blocks,
+                           state, list, equal, idx_out);
+        QAIA_HIP(hipGetLastError());
+        return;
+    }
     int64_t *d_n = (int64_t *)small;
     int32_t *d_passes = (int32_t *)(small + 8);
-    const float *src = scores;
-    if (temperature > 0.0f) {
-        hipLaunchKernelGGL(gumbel_keys_kernel, dim3(blocks_for(N)), dim3(kB), 0, st, scores, N, 1.0f / temperature,
-                           seed, pert);
-        src = pert;
-    }
     // stable: equal scores keep increasing index order; four passes leave the result in A
-    hipLaunchKernelGGL(topk_key_kernel, dim3(blocks_for(N)), dim3(kB), 0, st, src, N, keyA, valA, d_n, d_passes);
+    hipLaunchKernelGGL(topk_key_kernel, items, block, 0, st, scores, N, gumbel, inv_tau, seed, keyA, valA, d_n, d_passes);
     QAIA_HIP(hipGetLastError());
     for (int pass = 0; pass < 4; ++pass) {
         const bool even = (pass & 1) == 0;
         radix_pass(even ? keyA : keyB, even ? valA : valB, even ? keyB : keyA, even ? valB : valA, N, d_n, d_passes,
                    pass, hist, total, st);
     }
-    if (k > 0) {
-        hipLaunchKernelGGL(topk_out_kernel, dim3(blocks_for(k)), dim3(kB), 0, st, valA, k, idx_out);
-        QAIA_HIP(hipGetLastError());
-    }
+    hipLaunchKernelGGL(topk_out_kernel, dim3(blocks_for(k)), dim3(kB), 0, st, valA, k, idx_out);
+    QAIA_HIP(hipGetLastError());
 }
 
 void launch_labels(const int64_t *keep, const int64_t *num_keep, int64_t archive, int R, int64_t W,

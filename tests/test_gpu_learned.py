@@ -215,6 +215,23 @@ def test_topk_gather_and_labels(q):
     assert np.array_equal(lab, [1, 0, 1, 0, 1])
 
 
+@pytest.mark.parametrize("N,k", [(1, 1), (64, 64), (65, 3), (8191, 8191), (12288, 12288), (12289, 4096), (12289, 4097), (12289, 1),
+                                 (70001, 4096), (1100003, 777)])
+@pytest.mark.parametrize("kind", ["normal", "ties", "equal"])
+def test_topk_routes(q, N, k, kind):
+    """All pairs (up to 12 288 items), selection (at most 4096 of more) and the
+    radix sort on both sides of their limits, with ties at the k-th key."""
+    rng = np.random.default_rng(N + k)
+    s = rng.standard_normal(N).astype(np.float32)
+    if kind == "ties":
+        s = np.round(s, 1).astype(np.float32)
+    elif kind == "equal":
+        s[:] = -0.25
+        s[rng.integers(0, N, N // 1000 + 1)] = -0.125
+    s[rng.integers(0, N)] = -np.inf
+    assert np.array_equal(q.qaia_topk(_dev(s), k).cpu().numpy(), np.argsort(-s, kind="stable")[:k])
+
+
 def _race_rounds(q, prob, base, ref_rounds, contenders, seeds, cap=1.6):
     from paper_2604_26477_amd.learned import ProposerLoop, reference_run, time_to_hypervolume
     ref_hv, ref_s, _ = reference_run(prob, ref_rounds, 777, **base)
