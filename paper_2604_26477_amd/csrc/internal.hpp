@@ -58,6 +58,15 @@ struct DenseImages {
     float *scales = nullptr;  // device [3][8]: per precision, per objective
 };
 
+// Digit matrices of the weights for exact cut evaluation on the matrix cores
+// (cut.hip), upper triangles in MFMA operand order.
+struct CutImages {
+    bool ok = false;
+    int T = 0, L = 0;           // 32-spin tiles per side, base-256 digits per weight
+    int8_t *img = nullptr;      // [m L][T][T][64][16]
+    int64_t *total = nullptr;   // [m] sums of the weights
+};
+
 struct Problem {
     int32_t n = 0, m = 0, frac_bits = 0, device = 0;
     int64_t E = 0;
@@ -77,6 +86,7 @@ struct Problem {
     JitKernel *jit16[2][2][2] = {};  // [variant][trace][noise], binary16 form, built on first use
     std::string jit_error;
     DenseImages dense;
+    CutImages cut;
     std::mutex mu;
     ~Problem();
 };
@@ -186,6 +196,11 @@ void launch_random_spins(int n, int64_t count, uint64_t seed, uint64_t offset, u
 void launch_dirichlet(int m, int64_t count, uint64_t seed, uint64_t offset, float *out, hipStream_t st);
 void launch_evaluate(const Problem &p, const uint64_t *spins, int64_t count, int64_t *obj,
                      hipStream_t st);
+
+// cut evaluation on the matrix cores (cut.hip); needs p.cut.ok
+void cut_build(Problem &p);
+void cut_release(Problem &p);
+void launch_cut(const Problem &p, const uint64_t *spins, int64_t count, int64_t *obj, hipStream_t st);
 
 // generated kernels (jit.cpp)
 bool jit_eligible(const Problem &p, std::string *why);

@@ -723,6 +723,10 @@ void launch_evaluate(const Problem &p, const uint64_t *spins, int64_t count, int
                      hipStream_t st) {
     if (count == 0) return;
     QAIA_CHECK(p.m <= 8, QAIA_UNSUPPORTED, "evaluation supports at most 8 objectives");
+    if (p.cut.ok) {
+        launch_cut(p, spins, count, obj, st);
+        return;
+    }
     const size_t tile_lds = sizeof(uint32_t) * (size_t)kEvalTile * (2 * (size_t)p.words + 1);
     if (p.E <= 4096) {
         int64_t blocks = (count + kBlock - 1) / kBlock;

@@ -118,6 +118,29 @@ def test_evaluate_large_edge_sets(q, n, kind, count):
     assert np.array_equal(obj.cpu().numpy(), ref)
 
 
+@pytest.mark.parametrize("n,kind,m,bits,count", [
+    (12, "complete", 1, 7, 1), (31, "complete", 3, 20, 127), (32, "complete", 2, 8, 128), (33, "p0.5", 4, 17, 129),
+    (64, "complete", 8, 31, 300), (447, "p0.2", 3, 24, 70), (449, "complete", 8, 31, 130), (897, "p0.05", 3, 20, 2000),
+    (1200, "p0.01", 3, 20, 150)])
+def test_evaluate_digit_matrices(q, n, kind, m, bits, count):
+    """Cut values on the matrix cores at the edges of their tiles (32 spins, 128
+    samples, chunks of 448 spins), for one to five digits per weight (extreme
+    weights of the given bit length planted), and below the density where the
+    edges are walked instead."""
+    import torch
+    rng = np.random.default_rng(n + bits)
+    base = wl.random_instance(n, m, kind, seed=1300 + n)
+    hi = 2**bits - 1
+    w = rng.integers(-hi, hi, size=(m, base.num_edges), endpoint=True)
+    w[:, 0], w[:, -1] = hi, -hi
+    inst = wl.Instance(n, m, base.edge_u, base.edge_v, w.astype(np.int32))
+    prob = q.problem_from_instance(inst)
+    spins = q.qaia_random_spins(n, count, seed=10)
+    obj = q.qaia_evaluate(prob, spins)
+    torch.cuda.synchronize()
+    assert np.array_equal(obj.cpu().numpy(), oracle.cut_values(inst, unpack_spins(spins.cpu().numpy(), n)))
+
+
 @pytest.mark.parametrize("m", [2, 3, 4, 8])
 def test_dirichlet_weights_uniform_on_simplex(q, m):
     """Rows lie on the simplex, are reproducible and continue with offset, and
