@@ -14,6 +14,9 @@
 //   - branch B: dense items are set up, then each of the T steps is ONE launch
 //     of the grouped dense step kernel over the tiles of all dense items, then
 //     each dense item is read out and evaluated;
+//   - branches A, C and D in turn: the staged dense items that fit the resident
+//     kernel (all steps in one launch), each a launch of its own, since a small
+//     item holds few CUs;
 //   - the branches join and the caller's stream waits for the graph.
 // The kernel families differ in their tile shape and replicas per wave: one
 // replica per lane (64 replicas per wave, generated kernel), one spin per
@@ -83,6 +86,9 @@ void check_tile(const Problem &p, int path, int tile, int64_t rows) {
     (void)sparse_lds_shape(p, std::max<int64_t>(rows, 1), tile);  // throws past 16 spins per lane
 }
 
+bool is_resident(const ItemPlan &ip) { return ip.path == QAIA_PATH_DENSE_STAGED && resident_fits(*ip.p); }
+bool is_grouped_dense(const ItemPlan &ip) { return is_dense_path(ip.path) && !is_resident(ip); }
+
 struct BatchLayout {
     std::vector<ItemPlan> items;
     size_t jobs_off = 0, queue_off = 0, total = 0;
@@ -106,7 +112,7 @@ BatchLayout batch_layout(const qaia_batch_item *items, int32_t count, const qaia
         ItemPlan ip{&p, path, sample_ws_layout(p, it.W, it.R, s, !is_dense_path(path)), off};
         if (is_dense_path(path)) {
             dense_ws_extend(p, it.W, it.R, s, ip.L);
-            ++B.n_dense;
+            if (is_grouped_dense(ip)) ++B.n_dense;
         } else if (path == QAIA_PATH_SPARSE_LDS) {
             ++B.n_sparse;
         }
@@ -148,7 +154,7 @@ void reap_graphs() {
 }
 
 struct Streams {
-    hipStream_t a = nullptr, b = nullptr;
+    hipStream_t a = nullptr, b = nullptr, c = nullptr, d = nullptr;
 };
 std::mutex g_streams_mu;
 std::vector<Streams> g_streams;  // per device, default priority, created on first use
@@ -157,9 +163,11 @@ Streams private_streams(int device) {
     std::lock_guard<std::mutex> lk(g_streams_mu);
     if ((int)g_streams.size() <= device) g_streams.resize(device + 1);
     Streams &s = g_streams[device];
-    if (!s.a) {
+    if (!s.d) {
         QAIA_HIP(hipStreamCreateWithFlags(&s.a, hipStreamNonBlocking));
         QAIA_HIP(hipStreamCreateWithFlags(&s.b, hipStreamNonBlocking));
+        QAIA_HIP(hipStreamCreateWithFlags(&s.c, hipStreamNonBlocking));
+        QAIA_HIP(hipStreamCreateWithFlags(&s.d, hipStreamNonBlocking));
     }
     return s;
 }
@@ -222,7 +230,7 @@ void sample_batch(const qaia_batch_item *items, int32_t count, const qaia_schedu
             smaxdeg[c] = sh.maxdeg;
             snpt[c] = sh.npt;
             shmem[c] = std::max(shmem[c], sh.shmem);
-        } else if (is_dense_path(ip.path)) {
+        } else if (is_grouped_dense(ip)) {
             const int g = group_of(ip);
             DenseJob j = dense_job(*ip.p, it.W, it.R, s, iws, ip.L, nullptr, 0, g != 0);
             djobs[g].push_back(j);
@@ -271,11 +279,13 @@ void sample_batch(const qaia_batch_item *items, int32_t count, const qaia_schedu
     }
 
     Streams ps = private_streams(device);
-    hipEvent_t ev_start, ev_fork, ev_join, ev_done;
+    hipEvent_t ev_start, ev_fork, ev_join, ev_done, ev_side[2];
+    int forked = 0;  // side branches in use
     QAIA_HIP(hipEventCreateWithFlags(&ev_start, hipEventDisableTiming));
     QAIA_HIP(hipEventCreateWithFlags(&ev_fork, hipEventDisableTiming));
     QAIA_HIP(hipEventCreateWithFlags(&ev_join, hipEventDisableTiming));
     QAIA_HIP(hipEventCreateWithFlags(&ev_done, hipEventDisableTiming));
+    for (hipEvent_t &ev : ev_side) QAIA_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
     // the private stream follows the caller's prior work; descriptor uploads
     // are ordered there too (outside the graph)
     QAIA_HIP(hipEventRecord(ev_start, caller));
@@ -318,14 +328,27 @@ void sample_batch(const qaia_batch_item *items, int32_t count, const qaia_schedu
                 launch_sparse_reg(*ip.p, s.variant, it.W, it.R, s, base + ip.base, ip.L, it.spins, it.obj, nullptr, 0,
                                   ps.b);
         }
+        // resident dense items, dealt to three branches
+        const hipStream_t deal[3] = {ps.b, ps.c, ps.d};
+        for (int i = 0, turn = 0; i < count; ++i) {
+            const ItemPlan &ip = B.items[i];
+            const qaia_batch_item &it = items[i];
+            if (!is_resident(ip) || it.W * it.R == 0) continue;
+            const int d = turn++ % 3;
+            if (d > 0 && turn <= 3) QAIA_HIP(hipStreamWaitEvent(deal[d], ev_fork, 0));
+            launch_dense(*ip.p, it.weights, it.W, it.R, s, base + ip.base, ip.L, it.spins, it.obj, nullptr, 0, true,
+                         deal[d]);
+            forked = std::max(forked, d);
+        }
         QAIA_HIP(hipEventRecord(ev_join, ps.b));
+        for (int d = 1; d <= forked; ++d) QAIA_HIP(hipEventRecord(ev_side[d - 1], deal[d]));
         // branch B: dense items
         if (B.n_dense > 0) {
             int di[kGroups] = {0, 0, 0, 0, 0};
             for (int i = 0; i < count; ++i) {
                 const ItemPlan &ip = B.items[i];
                 const qaia_batch_item &it = items[i];
-                if (is_dense_path(ip.path) && it.W * it.R > 0) {
+                if (is_grouped_dense(ip) && it.W * it.R > 0) {
                     const int g = group_of(ip);
                     launch_dense_setup(*ip.p, it.weights, it.R, s, base + ip.base, ip.L, djobs[g][di[g]++], ps.a);
                 }
@@ -340,7 +363,7 @@ void sample_batch(const qaia_batch_item *items, int32_t count, const qaia_schedu
             for (int i = 0; i < count; ++i) {
                 const ItemPlan &ip = B.items[i];
                 const qaia_batch_item &it = items[i];
-                if (is_dense_path(ip.path) && it.W * it.R > 0) {
+                if (is_grouped_dense(ip) && it.W * it.R > 0) {
                     const int g = group_of(ip);
                     launch_dense_finish(*ip.p, it.R, s, base + ip.base, ip.L, djobs[g][di[g]++], it.spins, it.obj,
                                         ps.a);
@@ -348,6 +371,7 @@ void sample_batch(const qaia_batch_item *items, int32_t count, const qaia_schedu
             }
         }
         QAIA_HIP(hipStreamWaitEvent(ps.a, ev_join, 0));
+        for (int d = 1; d <= forked; ++d) QAIA_HIP(hipStreamWaitEvent(ps.a, ev_side[d - 1], 0));
     } catch (...) {
         hipGraph_t dropped = nullptr;
         (void)hipStreamEndCapture(ps.a, &dropped);
@@ -362,7 +386,7 @@ void sample_batch(const qaia_batch_item *items, int32_t count, const qaia_schedu
     QAIA_HIP(hipGraphLaunch(exec, ps.a));
     QAIA_HIP(hipEventRecord(ev_done, ps.a));
     QAIA_HIP(hipStreamWaitEvent(caller, ev_done, 0));
-    for (hipEvent_t ev : {ev_start, ev_fork, ev_join}) (void)hipEventDestroy(ev);
+    for (hipEvent_t ev : {ev_start, ev_fork, ev_join, ev_side[0], ev_side[1]}) (void)hipEventDestroy(ev);
     std::lock_guard<std::mutex> lk(g_pending_mu);
     g_pending.push_back({exec, ev_done});
 }

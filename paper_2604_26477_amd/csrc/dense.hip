@@ -1397,6 +1397,11 @@ void launch_dense(const Problem &p, const float *weights, int64_t W, int32_t R,
     const int64_t cols = W * (int64_t)R;
     if (cols == 0) return;
     QAIA_CHECK(L.colsP <= INT32_MAX / 2, QAIA_INVALID_ARGUMENT, "too many replicas for the dense path");
+    if (staged && resident_fits(p)) {
+        launch_resident(p, weights, W, R, s, ws, L, spins, trace, trace_steps, st);
+        launch_evaluate(p, spins, cols, obj, st);
+        return;
+    }
     const DenseJob j = dense_job(p, W, R, s, ws, L, trace, trace_steps, staged);
     launch_dense_setup(p, weights, R, s, ws, L, j, st);
     const dim3 grid(j.tiles_x, j.tiles_y);

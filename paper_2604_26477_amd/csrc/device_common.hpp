@@ -10,11 +10,13 @@ namespace qaia {
 // Counter-based SplitMix64 (Steele, Lea and Flood, OOPSLA 2014): the value
 // for counter idx is the (idx+1)-th output of the stream whose state starts
 // at seed (state += golden gamma, then the variant-13 finaliser).
-__device__ __forceinline__ uint64_t splitmix64(uint64_t seed, uint64_t idx) {
-    uint64_t z = seed + (idx + 1ull) * 0x9e3779b97f4a7c15ull;
+__device__ __forceinline__ uint64_t splitmix64_finish(uint64_t z) {
     z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
     z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
     return z ^ (z >> 31);
+}
+__device__ __forceinline__ uint64_t splitmix64(uint64_t seed, uint64_t idx) {
+    return splitmix64_finish(seed + (idx + 1ull) * 0x9e3779b97f4a7c15ull);
 }
 
 // Initial soft spin / momentum: 24-bit uniform u, v = 2u - 1 (exact in
@@ -46,8 +48,9 @@ __device__ __forceinline__ uint64_t init_counter(uint64_t g, int n, int i, int c
 //    the code whose 42 copies (one per spin of a generated kernel) did not fit
 //    the instruction cache.
 constexpr uint64_t kNoiseKey = 0xd1b54a32d192ed03ull;
-__device__ __forceinline__ float noise_value(uint64_t seed, uint64_t idx) {
-    const uint64_t bits = splitmix64(seed ^ kNoiseKey, idx);
+// (z: the stream's state at the draw, (seed ^ kNoiseKey) + (idx + 1) * gamma)
+__device__ __forceinline__ float noise_from(uint64_t z) {
+    const uint64_t bits = splitmix64_finish(z);
     const float u1 = (float)((uint32_t)(bits >> 40) + 1u) * 0x1p-24f;
     const float u2 = (float)(uint32_t)(bits & 0xffffffu) * 0x1p-24f;
     const float l2 = __builtin_amdgcn_logf(u1);
@@ -61,6 +64,9 @@ __device__ __forceinline__ float noise_value(uint64_t seed, uint64_t idx) {
     const float angle = 6.2831853071795864769f * u2;
     __builtin_assume(fabsf(angle) < 131072.0f);
     return radius * cosf(angle);
+}
+__device__ __forceinline__ float noise_value(uint64_t seed, uint64_t idx) {
+    return noise_from((seed ^ kNoiseKey) + (idx + 1ull) * 0x9e3779b97f4a7c15ull);
 }
 
 // sgn with sgn(0) = +1 (x is never -0 in these dynamics).

@@ -56,6 +56,11 @@ struct DenseImages {
     uint8_t *J8 = nullptr;    // e4m3 bits
     float scale16[8] = {}, scale8[8] = {};
     float *scales = nullptr;  // device [3][8]: per precision, per objective
+    // the same matrices in MFMA fragment order for small graphs (resident.hip), one allocation
+    void *frag = nullptr;
+    float *F32 = nullptr;
+    uint16_t *F16 = nullptr;
+    uint8_t *F8 = nullptr;
 };
 
 // Digit matrices of the weights for exact cut evaluation on the matrix cores
@@ -196,6 +201,13 @@ void launch_random_spins(int n, int64_t count, uint64_t seed, uint64_t offset, u
 void launch_dirichlet(int m, int64_t count, uint64_t seed, uint64_t offset, float *out, hipStream_t st);
 void launch_evaluate(const Problem &p, const uint64_t *spins, int64_t count, int64_t *obj,
                      hipStream_t st);
+
+// dense SB of small graphs, all steps in one launch (resident.hip)
+void resident_build(Problem &p);
+void resident_release(Problem &p);
+bool resident_fits(const Problem &p);
+void launch_resident(const Problem &p, const float *weights, int64_t W, int32_t R, const qaia_schedule &s, void *ws,
+                     const WsLayout &L, uint64_t *spins, float *trace, int32_t trace_steps, hipStream_t st);
 
 // cut evaluation on the matrix cores (cut.hip); needs p.cut.ok
 void cut_build(Problem &p);

@@ -48,6 +48,7 @@ Problem::~Problem() {
                 k = nullptr;
             }
     dense_release(*this);
+    resident_release(*this);
     cut_release(*this);
     DeviceGuard g(device);
     for (void *ptr : {(void *)d_eu, (void *)d_ev, (void *)d_W, (void *)d_rowptr, (void *)d_col,
@@ -148,6 +149,7 @@ Problem *build_problem(int32_t n, int32_t m, int64_t E, const int32_t *eu, const
         p->d_eid = upload(p->eid);
         p->d_rho = upload(rho);
         dense_build(*p);
+        resident_build(*p);
         cut_build(*p);
         jit_prepare(*p);
     } catch (...) {

@@ -265,3 +265,53 @@ def test_field_error_against_fp64(q):
     assert errs["bf16"][0] < 4e-3
     assert errs["fp8"][0] < 6e-2
     assert errs["fp32"][0] < errs["bf16"][0] < errs["fp8"][0]
+
+
+def _both_tiles(q, n, m, W, R, T, variant, prec, alpha, trace_steps=3, kind="complete", bad=()):
+    """Spins, cuts and the traced x of the staged path and of the register
+    tiles (64 x 128, one launch per step), which do the same arithmetic."""
+    import torch
+    inst = wl.random_instance(n, m, kind, seed=2100 + n)
+    p = q.problem_from_instance(inst)
+    c = wl.dirichlet_weights(W, m, 2200 + n)
+    for row in bad:
+        c[row] = -1.0
+    c = torch.from_numpy(c).cuda()
+    out = []
+    for path in ("dense_staged", "dense"):
+        s = q.make_schedule(variant, precision=prec, steps=T, dt=0.5, noise_alpha=alpha, seed=23, replica_offset=5,
+                            path=path)
+        spins, obj, ws, tr = q.qaia_sample_trace(p, c, R, s, trace_steps)
+        torch.cuda.synchronize()
+        assert q.qaia_workspace_status(ws) == (min(bad) if bad else None)
+        out.append([t.cpu().numpy() for t in (spins, obj, tr)])
+    return inst, out
+
+
+@pytest.mark.parametrize("n,m,W,R,T", [
+    (2, 1, 1, 1, 5), (31, 2, 3, 11, 40), (32, 3, 1, 32, 40), (33, 4, 11, 3, 40), (64, 1, 33, 1, 40), (65, 3, 5, 13, 40),
+    (97, 4, 3, 43, 40), (128, 2, 1, 127, 40), (255, 3, 4, 8, 25), (256, 4, 1, 33, 25), (257, 3, 2, 16, 25),
+    (509, 4, 3, 11, 15), (512, 3, 1, 64, 15)])
+@pytest.mark.parametrize("variant,prec,alpha", [("bsb", "fp32", 0.0), ("dsb", "fp32", 0.1), ("bsb", "fp32", 0.2),
+                                                ("dsb", "bf16", 0.0), ("dsb", "fp8", 0.1)])
+def test_resident_run_equals_register_tiles_bitwise(q, n, m, W, R, T, variant, prec, alpha):
+    """Up to 512 spins the staged path keeps a block's columns on chip for all
+    steps: edges of its 32-spin tiles, k-groups (8, 16, 64 spins), column tiles
+    (1, 2 or 4 per block, ragged) and wave counts (1 to 16), with an invalid
+    weight row where there is more than one."""
+    bad = (W - 1,) if W > 1 else ()
+    inst, (a, b) = _both_tiles(q, n, m, W, R, T, variant, prec, alpha, bad=bad)
+    for x, y in zip(a, b):
+        assert np.array_equal(x, y)
+    rows = W * R - len(bad) * R
+    assert np.array_equal(a[1][:rows], oracle.cut_values(inst, unpack_spins(a[0][:rows], n)))
+
+
+@pytest.mark.parametrize("n,m,W,R", [(513, 1, 3, 50), (520, 2, 2, 64), (600, 3, 1, 129), (640, 4, 5, 27)])
+@pytest.mark.parametrize("variant,prec,alpha", [("bsb", "fp32", 0.0), ("dsb", "fp32", 0.1), ("dsb", "bf16", 0.0),
+                                                ("dsb", "fp8", 0.0)])
+def test_staged_tiles_equal_register_tiles_bitwise(q, n, m, W, R, variant, prec, alpha):
+    """Past 512 spins the staged path launches its LDS tiles step by step."""
+    _, (a, b) = _both_tiles(q, n, m, W, R, 10, variant, prec, alpha)
+    for x, y in zip(a, b):
+        assert np.array_equal(x, y)
