@@ -122,9 +122,10 @@ int32_t sample_impl(const qaia_problem *pp, const float *weights, int64_t W, int
     else if (path == QAIA_PATH_SPARSE_REG)
         launch_sparse_reg(p, s->variant, W, R, *s, ws, L, spins, obj, trace_steps ? trace : nullptr,
                           trace_steps, st);
+    else if (sparse_group_fits(p))
+        launch_sparse_group(p, W, R, *s, ws, L, spins, obj, trace_steps ? trace : nullptr, trace_steps, st);
     else
-        launch_sparse_lds(p, W, R, *s, ws, L, spins, obj, trace_steps ? trace : nullptr,
-                          trace_steps, st);
+        launch_sparse_lds(p, W, R, *s, ws, L, spins, obj, trace_steps ? trace : nullptr, trace_steps, st);
     return QAIA_OK;
 }
 

@@ -62,7 +62,7 @@ __device__ __forceinline__ float noise_from(uint64_t z) {
     const float s0 = x * rs;
     const float radius = fmaf(fmaf(-s0, s0, x), 0.5f * rs, s0);
     const float angle = 6.2831853071795864769f * u2;
-    __builtin_assume(fabsf(angle) < 131072.0f);
+    __builtin_assume(__builtin_fabsf(angle) < 131072.0f);  // (fabsf, a call to the front end, would be ignored)
     return radius * cosf(angle);
 }
 __device__ __forceinline__ float noise_value(uint64_t seed, uint64_t idx) {

@@ -52,7 +52,7 @@ Problem::~Problem() {
     cut_release(*this);
     DeviceGuard g(device);
     for (void *ptr : {(void *)d_eu, (void *)d_ev, (void *)d_W, (void *)d_rowptr, (void *)d_col,
-                      (void *)d_eid, (void *)d_rho})
+                      (void *)d_eid, (void *)d_order, (void *)d_place, (void *)d_rho})
         if (ptr) (void)hipFree(ptr);
 }
 
@@ -148,6 +148,10 @@ Problem *build_problem(int32_t n, int32_t m, int64_t E, const int32_t *eu, const
         p->d_col = upload(p->col);
         p->d_eid = upload(p->eid);
         p->d_rho = upload(rho);
+        std::vector<int32_t> order, place;
+        group_order(*p, order, place);
+        p->d_order = upload(order);
+        p->d_place = upload(place);
         dense_build(*p);
         resident_build(*p);
         cut_build(*p);

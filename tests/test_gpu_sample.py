@@ -412,3 +412,55 @@ def test_noise_injected_sampling_exact_cuts(q, path):
     prob = q.problem_from_instance(inst)
     spins, obj, _ = _sample(q, prob, c, 16, steps=1000, seed=9, noise_alpha=0.15, path=path)
     assert np.array_equal(obj, oracle.cut_values(inst, unpack_spins(spins, inst.n)))
+
+
+@pytest.mark.parametrize("n,kind,W,R", [
+    (1, "deg3", 3, 5), (2, "complete", 3, 5), (31, "complete", 4, 7), (42, "deg3", 3, 5), (64, "p0.3", 5, 3), (65, "deg3", 3, 5),
+    (128, "p0.1", 2, 9), (129, "deg3", 3, 5), (130, "p0.12", 2, 4), (256, "deg3", 3, 3), (257, "p0.02", 3, 5), (512, "deg3", 2, 5),
+    (513, "deg3", 3, 5), (1024, "p0.005", 2, 3), (1025, "deg3", 1, 3),
+    # four replicas per lane (ragged last group), single waves and several, narrow and wide
+    (20, "deg3", 400, 70), (100, "deg3", 200, 30), (200, "deg3", 200, 15), (250, "p0.02", 100, 25), (200, "deg3", 300, 25),
+    (300, "p0.03", 100, 18), (400, "deg3", 300, 15), (700, "deg3", 100, 9), (700, "deg3", 150, 15), (600, "deg3", 3000, 1)])
+@pytest.mark.parametrize("variant", ["bsb", "dsb"])
+def test_one_spin_per_lane_shapes_equal_the_tiled_kernel(q, n, kind, W, R, variant):
+    """qaia_sample on the generic sparse path against the batch form's tiled
+    kernel, bit for bit, on both sides of every shape's limit (64, 128, 256, 512
+    and 1024 spins, degrees 3, 8 and 32), with an invalid weight row."""
+    import torch
+    inst = wl.random_instance(n, 3, kind, seed=2400 + n) if n > 1 else wl.Instance(
+        1, 3, np.zeros(0, np.int32), np.zeros(0, np.int32), np.zeros((3, 0), np.int32))
+    p = q.problem_from_instance(inst)
+    w = wl.dirichlet_weights(W, 3, 2500 + n)
+    w[W - 1] = 0.0
+    c = torch.from_numpy(w).cuda()
+    T = 65 if W * R * n < 10**6 else 12
+    s = q.make_schedule(variant, steps=T, seed=31, replica_offset=3, path="sparse_lds")
+    spins, obj, ws = q.qaia_sample(p, c, R, s)
+    item = q.BatchItem(p, c, R, "sparse_lds")
+    q.qaia_sample_batch([item], s)
+    torch.cuda.synchronize()
+    assert q.qaia_workspace_status(ws) == W - 1
+    assert torch.equal(spins, item.spins) and torch.equal(obj, item.obj)
+    assert not spins[(W - 1) * R:].any() and not obj[(W - 1) * R:].any()
+
+
+@pytest.mark.parametrize("n,kind,W,R", [(25, "complete", 3, 7), (100, "p0.1", 2, 9), (200, "deg3", 3, 4), (300, "p0.02", 2, 5),
+                                        (700, "deg3", 2, 3)])
+@pytest.mark.parametrize("variant", ["bsb", "dsb"])
+def test_one_spin_per_lane_noise_and_trace(q, n, kind, W, R, variant):
+    """The noise-injecting and tracing form against the tiled kernel (bits) and,
+    for the traced x, against the plain form's read-out of the last step."""
+    import torch
+    inst = wl.random_instance(n, 3, kind, seed=2600 + n)
+    p = q.problem_from_instance(inst)
+    c = torch.from_numpy(wl.dirichlet_weights(W, 3, 2700 + n)).cuda()
+    s = q.make_schedule(variant, steps=67, dt=1.0, noise_alpha=0.2, seed=37, replica_offset=11, path="sparse_lds")
+    spins, obj, _, tr = q.qaia_sample_trace(p, c, R, s, 67)
+    plain, pobj, _ = q.qaia_sample(p, c, R, s)
+    item = q.BatchItem(p, c, R, "sparse_lds")
+    q.qaia_sample_batch([item], s)
+    torch.cuda.synchronize()
+    for a, b in ((spins, plain), (obj, pobj), (spins, item.spins), (obj, item.obj)):
+        assert torch.equal(a, b)
+    last = unpack_spins(spins.cpu().numpy(), n)
+    assert np.array_equal(np.where(tr[:, -1].cpu().numpy() < 0, -1, 1), last)
