@@ -69,6 +69,17 @@ int plan_path(const Problem &p, const qaia_schedule &s, bool tracing) {
     return QAIA_PATH_DENSE_STAGED;
 }
 
+// Few replicas of a graph of the generated kernel, left to the library: that
+// kernel runs one replica per lane, so its time is one lane's chain of updates
+// until the replicas fill a wave per SIMD (65 536), while one spin per lane does a
+// step in the latency of one gather.  100 steps, generated against one spin per
+// lane, same bits: 42 nodes x 3200 replicas 76 / 31 us, x 20 000 77 / 63, x 40 000
+// 81 / 108; 20 nodes x 10 000 44 / 36, x 20 000 45 / 48; 12 nodes x 3200 35 / 32,
+// x 10 000 34 / 36; with noise 42 nodes x 3200 510 / 66, x 40 000 540 / 437.
+bool few_replicas(const Problem &p, int64_t rows, bool noise) {
+    return rows <= (noise ? 40000 : p.n >= 20 ? 16384 : 4096);
+}
+
 WsLayout full_layout(const Problem &p, int64_t W, int32_t R, const qaia_schedule &s, int path) {
     WsLayout L = sample_ws_layout(p, W, R, s, !is_dense_path(path));
     if (is_dense_path(path)) {
@@ -119,10 +130,18 @@ int32_t sample_impl(const qaia_problem *pp, const float *weights, int64_t W, int
     if (is_dense_path(path))
         launch_dense(p, weights, W, R, *s, ws, L, spins, obj, trace_steps ? trace : nullptr,
                      trace_steps, path == QAIA_PATH_DENSE_STAGED, st);
-    else if (path == QAIA_PATH_SPARSE_REG)
-        launch_sparse_reg(p, s->variant, W, R, *s, ws, L, spins, obj, trace_steps ? trace : nullptr,
-                          trace_steps, st);
-    else if (sparse_group_fits(p))
+    else if (path == QAIA_PATH_SPARSE_REG) {
+        const bool noise = s->dt * s->noise_alpha != 0.0f;
+        if (s->path == QAIA_PATH_AUTO && s->precision == QAIA_FP32 && trace_steps == 0 && sparse_group_fits(p) &&
+            few_replicas(p, rows, noise)) {
+            // the generated noise kernel is still built by the first call, for the calls that need it built
+            if (noise) jit_ensure(p, s->variant, true);
+            launch_sparse_group(p, W, R, *s, ws, L, spins, obj, nullptr, 0, st);
+        } else {
+            launch_sparse_reg(p, s->variant, W, R, *s, ws, L, spins, obj, trace_steps ? trace : nullptr, trace_steps,
+                              st);
+        }
+    } else if (sparse_group_fits(p))
         launch_sparse_group(p, W, R, *s, ws, L, spins, obj, trace_steps ? trace : nullptr, trace_steps, st);
     else
         launch_sparse_lds(p, W, R, *s, ws, L, spins, obj, trace_steps ? trace : nullptr, trace_steps, st);

@@ -222,6 +222,7 @@ void launch_cut(const Problem &p, const uint64_t *spins, int64_t count, int64_t 
 
 // generated kernels (jit.cpp)
 bool jit_eligible(const Problem &p, std::string *why);
+void jit_ensure(const Problem &p, int variant, bool noise);  // builds the FP32 kernel of the kind if it is not there yet
 void jit_prepare(Problem &p);  // compiles both variants if eligible; records failures
 void launch_sparse_reg(const Problem &p, int variant, int64_t W, int32_t R, const qaia_schedule &s,
                        void *ws, const WsLayout &L, uint64_t *spins, int64_t *obj, float *trace,

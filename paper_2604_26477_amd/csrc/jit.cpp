@@ -579,6 +579,8 @@ static const JitKernel *kernel_for(const Problem &p, int variant, bool trace, bo
     return slot;
 }
 
+void jit_ensure(const Problem &p, int variant, bool noise) { (void)kernel_for(p, variant, false, noise, false); }
+
 bool sparse_reg_ready(const Problem &p, int variant, bool trace, bool noise, bool half) {
     if (!trace && !noise && !half) return p.jit[variant] != nullptr;
     Problem &mp = const_cast<Problem &>(p);

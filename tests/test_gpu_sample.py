@@ -464,3 +464,26 @@ def test_one_spin_per_lane_noise_and_trace(q, n, kind, W, R, variant):
         assert torch.equal(a, b)
     last = unpack_spins(spins.cpu().numpy(), n)
     assert np.array_equal(np.where(tr[:, -1].cpu().numpy() < 0, -1, 1), last)
+
+
+@pytest.mark.parametrize("n,m,W,R", [(12, 2, 256, 16), (12, 2, 257, 16), (19, 3, 4097, 1), (20, 3, 1024, 16), (42, 8, 33, 7),
+                                     (42, 4, 1024, 16), (42, 4, 2341, 7), (70, 4, 5, 3), (56, 3, 625, 64), (56, 3, 626, 64)])
+@pytest.mark.parametrize("variant,alpha", [("bsb", 0.0), ("dsb", 0.0), ("dsb", 0.15)])
+def test_automatic_choice_of_few_replicas(q, n, m, W, R, variant, alpha):
+    """Left to the library, a graph of the generated kernel takes one spin per
+    lane for few replicas: both sides of the limits (4096, 16 384 and, with noise,
+    40 000 replicas) equal the generated kernel bit for bit."""
+    import torch
+    inst = wl.random_instance(n, m, "deg3", seed=2800 + n)
+    p = q.problem_from_instance(inst)
+    w = wl.dirichlet_weights(W, m, 2900 + n)
+    w[0] = 0.0
+    c = torch.from_numpy(w).cuda()
+    out = []
+    for path in ("auto", "sparse_reg"):
+        s = q.make_schedule(variant, steps=33, dt=0.5, noise_alpha=alpha, seed=41, replica_offset=9, path=path)
+        spins, obj, ws = q.qaia_sample(p, c, R, s)
+        torch.cuda.synchronize()
+        assert q.qaia_workspace_status(ws) == 0
+        out.append((spins, obj))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
