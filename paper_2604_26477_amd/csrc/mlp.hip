@@ -49,48 +49,58 @@ __device__ __forceinline__ float gelu_grad(float z) {
 
 // ---------------------------------------------------------------- MLP passes
 //
-// One block of 256 threads (four waves) handles 32 samples.  Layer 1
-// (D -> 128, tiny) runs on the vector units; the 128 x 128 contractions run
-// on the matrix cores as fp32 32x32x2 MFMAs (the bf16 weights widen exactly to
+// One block of sixteen waves handles 32 samples.  Layer 1 (D -> 128, tiny) and
+// the activations run on the vector units; the 128 x 128 contractions run on
+// the matrix cores as fp32 32x32x2 MFMAs (the bf16 weights widen exactly to
 // fp32, so activations and accumulation stay fp32):
-//   forward : Z2 = A1 W2^T, wave w takes the 32 units 32w .. 32w+31;
-//   backward: dZ1 = dZ2 W2 (wave w: hidden units 32w ..), and
-//             dW2 = dZ2^T A1 (wave w: rows u = 32w .., all 128 columns).
+//   forward : Z2 = A1 W2^T, waves 0 .. 3 take 32 units each;
+//   backward: dZ1 = dZ2 W2 (a wave per 32 hidden units), and
+//             dW2 = dZ2^T A1 (a wave per tile of 32 units x 32 columns).
 // For every MFMA the A and B fragments of a lane come from the same k
 // position (k = 2t + lane / 32), which pairs them for any internal k order.
 // Accumulator slot i of lane l holds row (i/4)*8 + (l/32)*4 + i%4, column l%32.
 // Training writes the block's gradient contribution (every parameter) to
-// partial[block]; a second kernel sums the blocks in a fixed order.
+// partial[block]; the blocks are summed in a fixed order.
+//
+// A batch of a few hundred samples leaves most of the chip idle and lasts one
+// block's chain, so that is kept short: sixteen waves share the activations
+// (some 60 instructions each, two per sample and unit in training), and with
+// Q = 4 four blocks repeat the forward part of a tile and take a quarter of the
+// hidden units' and of the columns' gradients each.  One 32-sample tile of
+// twelve inputs in training: 29 us with four waves and no split, now 15.
 constexpr int kS = 32;          // samples per block
 constexpr int kP = kH + 2;      // LDS pitch (floats) of the 128-wide tiles: a 32-lane strided read and its
                                 // neighbour column fall on disjoint banks
+constexpr int kT = 1024;
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 __device__ __forceinline__ int acc_row(int half, int i) { return (i >> 2) * 8 + half * 4 + (i & 3); }
 
-template <bool TRAIN>
-__global__ __launch_bounds__(kB) void mlp_fused_kernel(const uint16_t *__restrict__ P, int D,
-                                                       const float *__restrict__ X, int64_t N,
-                                                       const float *__restrict__ y, float *__restrict__ logits,
-                                                       float *__restrict__ partial) {
+template <bool TRAIN, int Q>
+__global__ __launch_bounds__(kT) void mlp_tile_kernel(const uint16_t *__restrict__ P, int D,
+                                                      const float *__restrict__ X, int64_t N,
+                                                      const float *__restrict__ y, float *__restrict__ logits,
+                                                      float *__restrict__ partial) {
     __shared__ float w2[kH * kP];          // W2[u][h] at u * kP + h
     __shared__ float w1[kH][kMaxD + 1];
     __shared__ float xs[kS][kMaxD + 1];
     __shared__ float a1[kS * kP];          // A1[s][h]
-    __shared__ float g1[TRAIN ? kS * kP : 1];   // gelu'(z1)[s][h]
-    __shared__ float dz2[TRAIN ? kS * kP : 1];  // dZ2[s][u]
-    __shared__ float dz1[TRAIN ? kS * kP : 1];  // dZ1[s][h]
-    __shared__ float lpart[4][kS];
+    __shared__ float z2[kS * kP];          // Z2[s][u], then dZ2
+    __shared__ float a2[TRAIN ? kS * kP : 1];   // gelu(Z2)
+    __shared__ float g2[TRAIN ? kS * kP : 1];   // gelu'(Z2)
+    __shared__ float g1[TRAIN ? kS * kP : 1];   // gelu'(z1)[s][h], then dZ1[s][h], of this block's h
     __shared__ float dz3[kS];
     const ParamOffsets o = offsets(D);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, lr = lane & 31;
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, lr = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), q = Q == 1 ? 0 : blockIdx.y;
     const int64_t s0 = (int64_t)blockIdx.x * kS;
     const int ns = (int)(N - s0 < kS ? N - s0 : kS);
     if ((((uintptr_t)(P + o.W2)) & 15) == 0) {
         // eight bf16 weights per 16-byte load (W2 starts at 128 (D + 1) elements)
         const uint4 *src = (const uint4 *)(P + o.W2);
-        for (int i = tid; i < kH * kH / 8; i += kB) {
+#pragma unroll
+        for (int i = tid; i < kH * kH / 8; i += kT) {
             const uint4 w = src[i];
             float *dst = w2 + ((i * 8) >> 7) * kP + ((i * 8) & (kH - 1));
             const uint32_t u[4] = {w.x, w.y, w.z, w.w};
@@ -101,75 +111,101 @@ __global__ __launch_bounds__(kB) void mlp_fused_kernel(const uint16_t *__restric
             }
         }
     } else {
-        for (int i = tid; i < kH * kH; i += kB) w2[(i >> 7) * kP + (i & (kH - 1))] = bf16_to_f32(P[o.W2 + i]);
+        for (int i = tid; i < kH * kH; i += kT) w2[(i >> 7) * kP + (i & (kH - 1))] = bf16_to_f32(P[o.W2 + i]);
     }
-    for (int i = tid; i < kH * kMaxD; i += kB) {
+    for (int i = tid; i < kH * kMaxD; i += kT) {
         const int h = i / kMaxD, d = i % kMaxD;
         w1[h][d] = d < D ? bf16_to_f32(P[o.W1 + (int64_t)h * D + d]) : 0.0f;
     }
-    for (int i = tid; i < kS * kMaxD; i += kB) {
-        const int s = i / kMaxD, d = i % kMaxD;
+    if (tid < kS * kMaxD) {
+        const int s = tid / kMaxD, d = tid % kMaxD;
         xs[s][d] = (s < ns && d < D) ? X[(s0 + s) * D + d] : 0.0f;
     }
+    float b1v[4], b2v[4], w3v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        b1v[j] = bf16_to_f32(P[o.b1 + 32 * j + (tid >> 5)]);
+        b2v[j] = bf16_to_f32(P[o.b2 + 32 * j + lr]);
+        w3v[j] = bf16_to_f32(P[o.w3 + 32 * j + lr]);
+    }
+    const float b3 = bf16_to_f32(P[o.b3]);
+    const int sr = 2 * wave + half;  // the sample of this half wave from layer 2 on
+    float yv = 0.0f;
+    if constexpr (TRAIN) yv = sr < ns ? y[s0 + sr] : 0.0f;
     __syncthreads();
-    // layer 1: thread t takes sample t % 32 and hidden units 16 (t / 32) ..
+    // layer 1: thread t takes sample t % 32 and hidden units t / 32 + 32 j
     {
         const int s = tid & (kS - 1), hg = tid >> 5;
-#pragma unroll 4
-        for (int j = 0; j < 16; ++j) {
-            const int h = hg * 16 + j;
-            float z = bf16_to_f32(P[o.b1 + h]);
-            for (int d = 0; d < D; ++d) z = fmaf(w1[h][d], xs[s][d], z);
-            a1[s * kP + h] = gelu(z);
-            if constexpr (TRAIN) g1[s * kP + h] = gelu_grad(z);
+        float z[4] = {b1v[0], b1v[1], b1v[2], b1v[3]};
+        for (int d = 0; d < D; ++d) {
+            const float x = xs[s][d];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) z[j] = fmaf(w1[32 * j + hg][d], x, z[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            a1[s * kP + 32 * j + hg] = gelu(z[j]);
+            if constexpr (TRAIN)
+                if (Q == 1 || j == q) g1[s * kP + 32 * j + hg] = gelu_grad(z[j]);
         }
     }
     __syncthreads();
-    // layer 2 on the matrix cores: this wave's 32 units
-    const int u = wave * 32 + lr;
-    f32x16 acc;
+    // layer 2 on the matrix cores: 32 units per wave
+    if (wave < 4) {
+        const int u = wave * 32 + lr;
+        f32x16 acc;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
-#pragma unroll 8
-    for (int t = 0; t < kH / 2; ++t) {
-        const int k = 2 * t + half;
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[lr * kP + k], w2[u * kP + k], acc, 0, 0, 0);
+        for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
+#pragma unroll 16
+        for (int t = 0; t < kH / 2; ++t) {
+            const int k = 2 * t + half;
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[lr * kP + k], w2[u * kP + k], acc, 0, 0, 0);
+        }
+        const float b2u = wave == 0 ? b2v[0] : wave == 1 ? b2v[1] : wave == 2 ? b2v[2] : b2v[3];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) z2[acc_row(half, i) * kP + u] = acc[i] + b2u;
     }
-    const float b2u = bf16_to_f32(P[o.b2 + u]), w3u = bf16_to_f32(P[o.w3 + u]);
-    float z2[16], part[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        z2[i] = acc[i] + b2u;
-        part[i] = w3u * gelu(z2[i]);
-    }
-    // head: sum over this wave's units (the 32 lanes of each half), per row
-#pragma unroll
-    for (int i = 0; i < 16; ++i)
-        for (int off = 16; off > 0; off >>= 1) part[i] += __shfl_xor(part[i], off, 64);
-    if (lr == 0)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) lpart[wave][acc_row(half, i)] = part[i];
     __syncthreads();
-    if (tid < kS) {
-        // the four waves' unit ranges in a fixed order
-        const float z = bf16_to_f32(P[o.b3]) + ((lpart[0][tid] + lpart[1][tid]) + (lpart[2][tid] + lpart[3][tid]));
-        if (tid < ns && logits) logits[s0 + tid] = z;
-        if constexpr (TRAIN) dz3[tid] = tid < ns ? (1.0f / (1.0f + expf(-z)) - y[s0 + tid]) / (float)N : 0.0f;
+    // head: half a wave per sample, summed over the 32 lanes of each unit tile,
+    // then over the four tiles in a fixed order
+    {
+        float z[4], a[4], part[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            z[j] = z2[sr * kP + 32 * j + lr];
+            a[j] = gelu(z[j]);
+            part[j] = fmaf(w3v[j], a[j], __shfl_xor(w3v[j] * a[j], 16, 64));
+        }
+        for (int off = 8; off > 0; off >>= 1)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) part[j] += __shfl_xor(part[j], off, 64);
+        // of the first lane: the fused first level makes the upper sixteen's sums other ones
+        const float lg = __shfl(b3 + ((part[0] + part[1]) + (part[2] + part[3])), lane & 32, 64);
+        if (lr == 0 && sr < ns && logits && q == 0) logits[s0 + sr] = lg;
+        if constexpr (!TRAIN) return;
+        // dZ2 = dz3 w3 gelu'(z2)
+        const float d3 = sr < ns ? (1.0f / (1.0f + expf(-lg)) - yv) / (float)N : 0.0f;
+        if (lr == 0) dz3[sr] = d3;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float g = gelu_grad(z[j]);
+            g2[sr * kP + 32 * j + lr] = g;
+            z2[sr * kP + 32 * j + lr] = d3 * w3v[j] * g;
+            a2[sr * kP + 32 * j + lr] = a[j];
+        }
     }
-    if constexpr (!TRAIN) return;
     __syncthreads();
     float *pg = partial + (int64_t)blockIdx.x * o.total;
-    // dZ2 = dz3 w3 gelu'(z2); gb2[u] = sum_s dZ2, gw3[u] = sum_s dz3 a2
-    {
+    // gb2[u] = sum_s dZ2, gw3[u] = sum_s dz3 a2: waves 4 .. (their SIMDs' matrix work is elsewhere or waits)
+    if (wave >= 4 && wave < 4 + (Q == 1 ? 4 : 1)) {
+        const int j = q + wave - 4, u = 32 * j + lr;
+        const float w3u = j == 0 ? w3v[0] : j == 1 ? w3v[1] : j == 2 ? w3v[2] : w3v[3];
         float gb2 = 0.0f, gw3 = 0.0f;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const int s = acc_row(half, i);
-            const float d3 = dz3[s];
-            const float d2 = d3 * w3u * gelu_grad(z2[i]);
-            dz2[s * kP + u] = d2;
-            gb2 += d2;
-            gw3 = fmaf(d3, gelu(z2[i]), gw3);
+            gb2 = fmaf(dz3[s] * w3u, g2[s * kP + u], gb2);
+            gw3 = fmaf(dz3[s], a2[s * kP + u], gw3);
         }
         gb2 += __shfl_xor(gb2, 32, 64);
         gw3 += __shfl_xor(gw3, 32, 64);
@@ -177,89 +213,246 @@ __global__ __launch_bounds__(kB) void mlp_fused_kernel(const uint16_t *__restric
             pg[o.b2 + u] = gb2;
             pg[o.w3 + u] = gw3;
         }
-        if (tid == 0) {
-            float g3 = 0.0f;
-            for (int s = 0; s < kS; ++s) g3 += dz3[s];
-            pg[o.b3] = g3;
-        }
     }
-    __syncthreads();
-    // dZ1 = (dZ2 W2) * gelu'(z1): this wave's hidden units h = 32w + lr
-    {
-        const int h = wave * 32 + lr;
+    if (tid == 8 * 64 && q == 0) {
+        float g3 = 0.0f;
+        for (int s = 0; s < kS; ++s) g3 += dz3[s];
+        pg[o.b3] = g3;
+    }
+    // dZ1 = (dZ2 W2) * gelu'(z1)
+    if (wave < (Q == 1 ? 4 : 1)) {
+        const int h = 32 * (q + wave) + lr;
         f32x16 d;
 #pragma unroll
         for (int i = 0; i < 16; ++i) d[i] = 0.0f;
-#pragma unroll 8
+#pragma unroll 16
         for (int t = 0; t < kH / 2; ++t) {
             const int k = 2 * t + half;  // the unit index u
-            d = __builtin_amdgcn_mfma_f32_32x32x2f32(dz2[lr * kP + k], w2[k * kP + h], d, 0, 0, 0);
+            d = __builtin_amdgcn_mfma_f32_32x32x2f32(z2[lr * kP + k], w2[k * kP + h], d, 0, 0, 0);
         }
         float gb1 = 0.0f;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const int s = acc_row(half, i);
-            const float v = d[i] * g1[s * kP + h];
-            dz1[s * kP + h] = v;
-            gb1 += v;
+            const float v = g1[s * kP + h];
+            g1[s * kP + h] = d[i] * v;
+            gb1 = fmaf(d[i], v, gb1);
         }
         gb1 += __shfl_xor(gb1, 32, 64);
         if (half == 0) pg[o.b1 + h] = gb1;
     }
-    // dW2 = dZ2^T A1: rows u = 32w + .., columns h in four 32-wide tiles, k = sample
+    // dW2 = dZ2^T A1: a tile of rows u and columns h per wave, k = sample.  With
+    // Q = 4 the tiles go to waves 1, 2, 3 and 5: wave 0's SIMD has the longer chain of dZ1
+    {
+        const int r = Q == 1 ? wave & 3 : wave == 5 ? 3 : wave - 1, c = Q == 1 ? wave >> 2 : q;
+        if (Q == 1 || (wave >= 1 && wave <= 5 && wave != 4)) {
+            f32x16 g;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        f32x16 g;
+            for (int i = 0; i < 16; ++i) g[i] = 0.0f;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) g[i] = 0.0f;
+            for (int t = 0; t < kS / 2; ++t) {
+                const int s = 2 * t + half;
+                g = __builtin_amdgcn_mfma_f32_32x32x2f32(z2[s * kP + r * 32 + lr], a1[s * kP + c * 32 + lr], g, 0, 0, 0);
+            }
 #pragma unroll
-        for (int t = 0; t < kS / 2; ++t) {
-            const int s = 2 * t + half;
-            g = __builtin_amdgcn_mfma_f32_32x32x2f32(dz2[s * kP + wave * 32 + lr], a1[s * kP + c * 32 + lr], g, 0, 0,
-                                                     0);
+            for (int i = 0; i < 16; ++i) pg[o.W2 + (int64_t)(r * 32 + acc_row(half, i)) * kH + c * 32 + lr] = g[i];
         }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) pg[o.W2 + (int64_t)(wave * 32 + acc_row(half, i)) * kH + c * 32 + lr] = g[i];
     }
     __syncthreads();
-    // dW1[h][d] = sum_s dZ1[s][h] x[s][d]: thread t takes hidden unit t / 2 and eight inputs
-    {
-        const int h = tid >> 1, d0 = (tid & 1) * 8;
-        float g[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        for (int s = 0; s < kS; ++s) {
-            const float v = dz1[s * kP + h];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) g[j] = fmaf(v, xs[s][d0 + j], g[j]);
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-            if (d0 + j < D) pg[o.W1 + (int64_t)h * D + d0 + j] = g[j];
+    // dW1[h][d] = sum_s dZ1[s][h] x[s][d]: a thread per entry
+    for (int i = tid; i < kH / Q * kMaxD; i += kT) {
+        const int h = kH / Q * q + i / kMaxD, d = i % kMaxD;
+        float g = 0.0f;
+#pragma unroll 8
+        for (int s = 0; s < kS; ++s) g = fmaf(g1[s * kP + h], xs[s][d], g);
+        if (d < D) pg[o.W1 + (int64_t)h * D + d] = g;
     }
 }
 
-// the gradient is the sum of the blocks' contributions, in block order (deterministic)
+// Forward of many samples: one wave takes 32 samples through the whole network
+// and keeps them in registers.  The operands of layer 2 are the other way round
+// (rows = units, columns = samples), so lane l holds sample l % 32: it computes
+// the hidden unit that its half contributes to the next MFMA itself, k by k, and
+// the four unit tiles take it at once (four accumulators; no layer-1 tile in
+// LDS, no barrier).  The 16 units of a lane's accumulator are summed in the
+// order of the other kernel's shuffles (unit bits 4, 3, 2, 1, 0), four of the
+// five levels of them in the lane.  Weights lie in LDS widened, W2 as
+// [k parity][k / 8][unit][4]: one 16-byte read per four MFMAs, conflict-free
+// when read and, with the pitch of 516, when filled along k.
+// Bound by the vector unit: 256 gelus of some 57 instructions per sample, 28 us
+// for 65 536 samples if nothing else ran; the MFMAs lie between them.  That many
+// samples of twelve inputs: 133 us with a block of four waves per 32, now 46.
+constexpr int kRWaves = 8;
+constexpr int kW2Pitch = 4 * kH + 4;
+constexpr int kW2Parity = 16 * kW2Pitch + 16;
+
+template <int G>  // groups of four inputs
+__global__ __launch_bounds__(64 * kRWaves) void mlp_rows_kernel(const uint16_t *__restrict__ P, int D,
+                                                                const float *__restrict__ X, int64_t N,
+                                                                float *__restrict__ logits) {
+    __shared__ __align__(16) float w2[2 * kW2Parity];
+    __shared__ __align__(16) float w1[kH * 4 * G];
+    __shared__ __align__(16) float b1[2 * kH / 2], b2[kH], w3[kH];
+    const ParamOffsets o = offsets(D);
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, lr = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool wide = (((uintptr_t)(P + o.W2)) & 15) == 0;  // W2 starts at 128 (D + 1) elements
+    for (int i = tid; i < kH * kH / 8; i += 64 * kRWaves) {
+        const int u = i >> 4, c = i & 15;  // eight weights k = 8c .. of unit u
+        uint4 w;
+        if (wide) {
+            w = ((const uint4 *)(P + o.W2))[i];
+        } else {
+            const uint16_t *q = P + o.W2 + 8 * i;
+            w = make_uint4(q[0] | (uint32_t)q[1] << 16, q[2] | (uint32_t)q[3] << 16, q[4] | (uint32_t)q[5] << 16,
+                           q[6] | (uint32_t)q[7] << 16);
+        }
+        float *dst = w2 + c * kW2Pitch + 4 * u;
+        *(float4 *)dst = make_float4(__uint_as_float(w.x << 16), __uint_as_float(w.y << 16),
+                                     __uint_as_float(w.z << 16), __uint_as_float(w.w << 16));
+        *(float4 *)(dst + kW2Parity) =
+            make_float4(__uint_as_float(w.x & 0xFFFF0000u), __uint_as_float(w.y & 0xFFFF0000u),
+                        __uint_as_float(w.z & 0xFFFF0000u), __uint_as_float(w.w & 0xFFFF0000u));
+    }
+    for (int i = tid; i < kH * 4 * G; i += 64 * kRWaves) {
+        const int h = i / (4 * G), d = i % (4 * G);
+        w1[i] = d < D ? bf16_to_f32(P[o.W1 + (int64_t)h * D + d]) : 0.0f;
+    }
+    if (tid < kH) {
+        b1[(tid & 1) * (kH / 2) + (tid >> 1)] = bf16_to_f32(P[o.b1 + tid]);
+        b2[tid] = bf16_to_f32(P[o.b2 + tid]);
+        w3[tid] = bf16_to_f32(P[o.w3 + tid]);
+    }
+    const float b3 = bf16_to_f32(P[o.b3]);
+    __syncthreads();
+    const float *wl = w2 + half * kW2Parity + 4 * lr;
+    const float *w1l = w1 + half * 4 * G;
+    const float *b1l = b1 + half * (kH / 2);
+    for (int64_t tile = blockIdx.x + (int64_t)gridDim.x * wave; tile * kS < N; tile += (int64_t)gridDim.x * kRWaves) {
+        const int64_t s = tile * kS + lr;
+        float x[4 * G];
+#pragma unroll
+        for (int d = 0; d < 4 * G; ++d) {  // 0 * -0 + z is z for every z
+            x[d] = X[(s < N ? s : N - 1) * D + (d < D ? d : D - 1)];
+            if (d >= D) x[d] = -0.0f;
+        }
+        auto hidden = [&](int c, float *a) {
+            const float4 bb = *(const float4 *)(b1l + 4 * c);
+            const float zb[4] = {bb.x, bb.y, bb.z, bb.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float z = zb[e];
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    const float4 w = *(const float4 *)(w1l + (8 * c + 2 * e) * 4 * G + 4 * g);
+                    z = fmaf(w.x, x[4 * g], z);
+                    z = fmaf(w.y, x[4 * g + 1], z);
+                    z = fmaf(w.z, x[4 * g + 2], z);
+                    z = fmaf(w.w, x[4 * g + 3], z);
+                }
+                a[e] = gelu(z);
+            }
+        };
+        f32x16 acc[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[j][i] = 0.0f;
+        float a[4];
+        hidden(0, a);
+#pragma unroll 1
+        for (int c = 0; c < 16; ++c) {
+            float next[4];
+            float4 w[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) w[j] = *(const float4 *)(wl + c * kW2Pitch + 128 * j);
+            hidden((c + 1) & 15, next);  // the last one is not used
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float we = e == 0 ? w[j].x : e == 1 ? w[j].y : e == 2 ? w[j].z : w[j].w;
+                    acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(we, a[e], acc[j], 0, 0, 0);
+                }
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // an MFMA takes 64 cycles,
+                __builtin_amdgcn_sched_group_barrier(0x002, 17, 0);  // as do 16 to 17 of the next hidden units' instructions
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[e] = next[e];
+        }
+        float l0 = 0.0f, l1 = 0.0f, l2 = 0.0f, l3 = 0.0f;
+#pragma unroll 1
+        for (int j = 0; j < 4; ++j) {
+            float p[16];
+#pragma unroll
+            for (int i = 12; i >= 0; i -= 4) {
+                const float4 b = *(const float4 *)(b2 + 32 * j + acc_row(half, i));
+                const float4 w = *(const float4 *)(w3 + 32 * j + acc_row(half, i));
+                const float bw[4] = {b.x, b.y, b.z, b.w}, ww[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float g = gelu(acc[0][i + e] + bw[e]);
+                    p[i + e] = i >= 8 ? ww[e] * g : fmaf(ww[e], g, p[i + e + 8]);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                p[i] += p[i + 4];
+                p[i] += __shfl_xor(p[i], 32, 64);
+            }
+            l0 = l1;
+            l1 = l2;
+            l2 = l3;
+            l3 = (p[0] + p[2]) + (p[1] + p[3]);
+            acc[0] = acc[1];
+            acc[1] = acc[2];
+            acc[2] = acc[3];
+        }
+        if (half == 0 && s < N) logits[s] = b3 + ((l0 + l1) + (l2 + l3));
+    }
+}
+
+// the gradient is the sum of the blocks' contributions, in block order (deterministic);
+// the loads of sixteen blocks are in flight at once
+__device__ __forceinline__ float grad_sum(const float *__restrict__ partial, int slices, int64_t total, int64_t p) {
+    float g = 0.0f;
+    int j = 0;
+    for (; j + 16 <= slices; j += 16) {
+        float v[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) v[e] = partial[(int64_t)(j + e) * total + p];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) g += v[e];
+    }
+    for (; j < slices; ++j) g += partial[(int64_t)j * total + p];
+    return g;
+}
+
 __global__ void grads_reduce_kernel(const float *__restrict__ partial, int slices, int64_t total,
                                     float *__restrict__ grad) {
     const int64_t p = (int64_t)blockIdx.x * kB + threadIdx.x;
-    if (p >= total) return;
-    float g = 0.0f;
-    for (int j = 0; j < slices; ++j) g += partial[(int64_t)j * total + p];
-    grad[p] = g;
+    if (p < total) grad[p] = grad_sum(partial, slices, total, p);
 }
 
-// Adam (Kingma and Ba, 2015) on fp32 master weights; refreshes the bf16 copy
+// Adam (Kingma and Ba, 2015) on fp32 master weights; refreshes the bf16 copy.
+// The gradient is g[n] (slices = 0) or, in the training loop, the sum of the
+// blocks' contributions, which then takes no kernel of its own (8.5 + 4.8 us for
+// 32 blocks, now 4.7).
 __global__ void adam_kernel(float *__restrict__ master, uint16_t *__restrict__ P,
                             float *__restrict__ m, float *__restrict__ v,
-                            const float *__restrict__ g, int64_t n, float lr, float b1, float b2,
+                            const float *__restrict__ g, int slices, int64_t n, float lr, float b1, float b2,
                             float eps, float c1, float c2) {
     const int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x;
     if (i >= n) return;
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.0f - b1) * gi;
-    const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
+    const float m0 = m[i], v0 = v[i], w0 = master[i];
+    const float gi = slices ? grad_sum(g, slices, n, i) : g[i];
+    const float mi = fmaf(1.0f - b1, gi, b1 * m0);
+    const float vi = fmaf((1.0f - b2) * gi, gi, b2 * v0);
     m[i] = mi;
     v[i] = vi;
-    const float w = master[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+    const float w = w0 - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
     master[i] = w;
     P[i] = f32_to_bf16(w);
 }
@@ -888,6 +1081,14 @@ size_t mlp_forward_ws_bytes(int64_t N) {
     return 256;  // the fused forward keeps everything on chip
 }
 
+// A wave alone with a tile needs 30 us however few there are, a block with a tile
+// 11, one per CU at a time: 8192 samples 11 against 30 us, 16 384 19 / 30, 24 000
+// 27.5 / 30, and a fourth round of the blocks would be slower than the 30 us of 32 768.
+constexpr int64_t kRowsMin = 24576;
+// Four blocks per tile while they all run at once, one per CU: 64 tiles 15.6 us
+// split, 23 whole; at 65 tiles the split would take a second round.
+constexpr int64_t kSplitMax = 64;
+
 void launch_mlp_forward(const uint16_t *P, int D, const float *X, int64_t N, float *logits, void *ws,
                         hipStream_t st) {
     (void)ws;
@@ -895,33 +1096,61 @@ void launch_mlp_forward(const uint16_t *P, int D, const float *X, int64_t N, flo
     if (N == 0) return;
     const int64_t blocks = grad_blocks(N);
     QAIA_CHECK(blocks <= INT32_MAX, QAIA_INVALID_ARGUMENT, "too many samples");
-    hipLaunchKernelGGL(mlp_fused_kernel<false>, dim3((unsigned)blocks), dim3(kB), 0, st, P, D, X, N,
-                       (const float *)nullptr, logits, (float *)nullptr);
+    if (N > kRowsMin) {
+        // 256 blocks give up to eight tiles per CU to different SIMDs; above, two blocks share a CU
+        // (262 144 samples 168 us with 256 blocks, 158 with 512; 16 385 29 and 43)
+        const unsigned rows_blocks = blocks <= 256 * kRWaves ? 256 : 512;
+        const auto k = D <= 4    ? mlp_rows_kernel<1>
+                       : D <= 8  ? mlp_rows_kernel<2>
+                       : D <= 12 ? mlp_rows_kernel<3>
+                                 : mlp_rows_kernel<4>;
+        hipLaunchKernelGGL(k, dim3((unsigned)rows_blocks), dim3(64 * kRWaves), 0, st, P, D, X, N,
+                           logits);
+    } else {
+        hipLaunchKernelGGL((mlp_tile_kernel<false, 1>), dim3((unsigned)blocks), dim3(kT), 0, st, P, D, X, N,
+                           (const float *)nullptr, logits, (float *)nullptr);
+    }
     QAIA_HIP(hipGetLastError());
+}
+
+static int launch_mlp_partial(const uint16_t *P, int D, const float *X, const float *y, int64_t B, float *logits,
+                              float *partial, hipStream_t st) {
+    QAIA_CHECK(D >= 1 && D <= kMaxD, QAIA_INVALID_ARGUMENT, "input width must be in [1, 16]");
+    QAIA_CHECK(B >= 1, QAIA_INVALID_ARGUMENT, "batch must be >= 1");
+    const int64_t blocks = grad_blocks(B);
+    QAIA_CHECK(blocks <= 65535, QAIA_INVALID_ARGUMENT, "batch too large");
+    if (blocks <= kSplitMax)
+        hipLaunchKernelGGL((mlp_tile_kernel<true, 4>), dim3((unsigned)blocks, 4), dim3(kT), 0, st, P, D, X, B, y,
+                           logits, partial);
+    else
+        hipLaunchKernelGGL((mlp_tile_kernel<true, 1>), dim3((unsigned)blocks), dim3(kT), 0, st, P, D, X, B, y, logits,
+                           partial);
+    QAIA_HIP(hipGetLastError());
+    return (int)blocks;
 }
 
 void launch_mlp_backward(const uint16_t *P, int D, const float *X, const float *y, int64_t B,
                          float *grad, float *loss_logits, void *ws, hipStream_t st) {
-    QAIA_CHECK(D >= 1 && D <= kMaxD, QAIA_INVALID_ARGUMENT, "input width must be in [1, 16]");
-    QAIA_CHECK(B >= 1, QAIA_INVALID_ARGUMENT, "batch must be >= 1");
-    const int64_t total = offsets(D).total, blocks = grad_blocks(B);
-    QAIA_CHECK(blocks <= 65535, QAIA_INVALID_ARGUMENT, "batch too large");
     float *partial = (float *)ws;
-    hipLaunchKernelGGL(mlp_fused_kernel<true>, dim3((unsigned)blocks), dim3(kB), 0, st, P, D, X, B, y, loss_logits,
-                       partial);
-    hipLaunchKernelGGL(grads_reduce_kernel, dim3(blocks_for(total)), dim3(kB), 0, st, partial, (int)blocks, total,
-                       grad);
+    const int blocks = launch_mlp_partial(P, D, X, y, B, loss_logits, partial, st);
+    const int64_t total = offsets(D).total;
+    hipLaunchKernelGGL(grads_reduce_kernel, dim3(blocks_for(total)), dim3(kB), 0, st, partial, blocks, total, grad);
+    QAIA_HIP(hipGetLastError());
+}
+
+static void launch_adam_step(float *master, uint16_t *P, float *m, float *v, const float *g, int slices, int64_t n,
+                             int step, float lr, float b1, float b2, float eps, hipStream_t st) {
+    QAIA_CHECK(step >= 1, QAIA_INVALID_ARGUMENT, "Adam step counts from 1");
+    const float c1 = (float)(1.0 - std::pow((double)b1, step));
+    const float c2 = (float)(1.0 - std::pow((double)b2, step));
+    hipLaunchKernelGGL(adam_kernel, dim3(blocks_for(n)), dim3(kB), 0, st, master, P, m, v, g, slices, n, lr, b1,
+                       b2, eps, c1, c2);
     QAIA_HIP(hipGetLastError());
 }
 
 void launch_adam(float *master, uint16_t *P, float *m, float *v, const float *g, int64_t n, int step,
                  float lr, float b1, float b2, float eps, hipStream_t st) {
-    QAIA_CHECK(step >= 1, QAIA_INVALID_ARGUMENT, "Adam step counts from 1");
-    const float c1 = (float)(1.0 - std::pow((double)b1, step));
-    const float c2 = (float)(1.0 - std::pow((double)b2, step));
-    hipLaunchKernelGGL(adam_kernel, dim3(blocks_for(n)), dim3(kB), 0, st, master, P, m, v, g, n, lr, b1,
-                       b2, eps, c1, c2);
-    QAIA_HIP(hipGetLastError());
+    launch_adam_step(master, P, m, v, g, 0, n, step, lr, b1, b2, eps, st);
 }
 
 // ---------------------------------------------------------------- training loop
@@ -933,7 +1162,7 @@ __global__ void train_count_kernel(int64_t *c, int64_t n) {
 }  // namespace
 
 struct TrainLayout {
-    size_t zeros, perm, xp, yp, grad, count, bw, tk, total;
+    size_t zeros, perm, xp, yp, count, bw, tk, total;
 };
 
 static TrainLayout train_layout(int D, int64_t n, int64_t B) {
@@ -949,7 +1178,6 @@ static TrainLayout train_layout(int D, int64_t n, int64_t B) {
     L.perm = take(sizeof(int64_t) * nz);
     L.xp = take(sizeof(float) * nz * (size_t)D);
     L.yp = take(sizeof(float) * nz);
-    L.grad = take(sizeof(float) * (size_t)offsets(D).total);
     L.count = take(sizeof(int64_t));
     L.bw = take(mlp_backward_ws_bytes(D, B));
     L.tk = take(topk_ws_bytes(n));
@@ -977,7 +1205,6 @@ void launch_mlp_train(float *master, uint16_t *P, float *m1, float *m2, int D, c
     QAIA_CHECK(ws_bytes >= L.total, QAIA_WORKSPACE_TOO_SMALL, "training workspace too small");
     char *b = (char *)ws;
     float *zeros = (float *)(b + L.zeros), *xp = (float *)(b + L.xp), *yp = (float *)(b + L.yp);
-    float *grad = (float *)(b + L.grad);
     int64_t *perm = (int64_t *)(b + L.perm), *cnt = (int64_t *)(b + L.count);
     const int64_t total = offsets(D).total;
     hipLaunchKernelGGL(zero_f32_kernel, dim3(blocks_for(n)), dim3(kB), 0, st, zeros, n);
@@ -991,8 +1218,9 @@ void launch_mlp_train(float *master, uint16_t *P, float *m1, float *m2, int D, c
             launch_gather_rows((const uint32_t *)X, D, perm, cnt, n, (uint32_t *)xp, st);
             launch_gather_rows((const uint32_t *)y, 1, perm, cnt, n, (uint32_t *)yp, st);
         }
-        launch_mlp_backward(P, D, xp + win * B * D, yp + win * B, B, grad, nullptr, b + L.bw, st);
-        launch_adam(master, P, m1, m2, grad, total, first_step + t, lr, 0.9f, 0.999f, 1e-8f, st);
+        float *partial = (float *)(b + L.bw);
+        const int blocks = launch_mlp_partial(P, D, xp + win * B * D, yp + win * B, B, nullptr, partial, st);
+        launch_adam_step(master, P, m1, m2, partial, blocks, total, first_step + t, lr, 0.9f, 0.999f, 1e-8f, st);
     }
 }
 

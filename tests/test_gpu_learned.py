@@ -279,3 +279,37 @@ def test_combined_form_reaches_reference_first(q):
           f"{form['seconds']} s")
     assert form["reached"]
     assert not plain["reached"] or form["seconds"] < plain["seconds"]
+
+
+@pytest.mark.parametrize("D,N,shift", [(1, 24577, 0), (4, 24590, 0), (5, 24608, 1), (8, 30001, 0), (9, 65536, 0),
+                                       (12, 65537, 8), (13, 70000, 1), (16, 140001, 0)])
+def test_forward_of_many_samples(q, D, N, shift):
+    """Above 24 576 samples a wave takes 32 samples on its own: the same logits,
+    bit for bit, as smaller calls (a block per 32), for every width of
+    the input padding, aligned and unaligned parameters, and with blocks that
+    take several tiles."""
+    import torch
+    _, _, bits = _params(D, 40 + D)
+    X = _dev(np.random.default_rng(41).standard_normal((N, D)).astype(np.float32))
+    X[:, 0] = torch.where(X[:, 0].abs() < 0.05, torch.zeros_like(X[:, 0]), X[:, 0] * 4)
+    P = torch.zeros(len(bits) + shift, dtype=torch.int16, device="cuda")
+    P[shift:] = _dev(bits.view(np.int16))
+    got = q.qaia_mlp_forward(P[shift:], D, X)
+    want = torch.cat([q.qaia_mlp_forward(_dev(bits.view(np.int16)), D, X[i:i + 8191].contiguous())
+                      for i in range(0, N, 8191)])
+    assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("D,B", [(5, 33), (12, 2048), (12, 2049), (1, 2080)])
+def test_backward_split_and_whole_tiles(q, D, B):
+    """Up to 64 tiles of 32 samples four blocks share a tile's gradient, above
+    one block computes it: both against the oracle within the bound of
+    test_backward_matches_oracle."""
+    _, vals, bits = _params(D, 43)
+    rng = np.random.default_rng(44)
+    X = rng.standard_normal((B, D)).astype(np.float32)
+    y = rng.integers(0, 2, size=B).astype(np.float32)
+    got = q.qaia_mlp_backward(_dev(bits.view(np.int16)), D, _dev(X), _dev(y)).cpu().numpy()
+    want = omlp.backward(vals, X.astype(np.float64), y.astype(np.float64), D)
+    scale = _grad_magnitude(vals, X.astype(np.float64), y.astype(np.float64), D)
+    assert (np.abs(got - want) <= 1e-3 * np.abs(want) + 1e-5 * scale).all()
