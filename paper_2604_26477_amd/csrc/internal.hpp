@@ -61,6 +61,8 @@ struct DenseImages {
     float *F32 = nullptr;
     uint16_t *F16 = nullptr;
     uint8_t *F8 = nullptr;
+    int8_t *FD = nullptr;  // base-256 digits of the weights (exact discrete products)
+    int digits = 0;        // per weight; 0: not exact, FP32 products instead
 };
 
 // Digit matrices of the weights for exact cut evaluation on the matrix cores

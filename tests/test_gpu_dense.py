@@ -315,3 +315,42 @@ def test_staged_tiles_equal_register_tiles_bitwise(q, n, m, W, R, variant, prec,
     _, (a, b) = _both_tiles(q, n, m, W, R, 10, variant, prec, alpha)
     for x, y in zip(a, b):
         assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("n,W,R", [(5, 3, 50), (40, 5, 13), (70, 2, 64), (100, 3, 43), (130, 2, 33), (190, 1, 32),
+                                   (200, 3, 11), (250, 2, 40), (300, 1, 65), (321, 2, 16)])
+@pytest.mark.parametrize("largest,alpha", [(127, 0.1), (128, 0.0), (32639, 0.0), (32640, 0.1), ("edge", 0.1), ("over", 0.1),
+                                           (8355711, 0.0), (8355712, 0.0)])
+def test_exact_digits_equal_register_tiles_bitwise(q, n, W, R, largest, alpha):
+    """Discrete SB in single precision multiplies base-256 digits where rounding
+    cannot differ: one, two and three digits at their largest weights, every
+    number of 32-spin groups, a row whose weights add up to 2^24 - 1 (exact) and
+    to 2^24 (the FP32 product), against the register tiles' FP32 product."""
+    import torch
+    m = 1 + n % 4
+    u, v = np.triu_indices(n, 1)
+    rng = np.random.default_rng(n)
+    if isinstance(largest, str):
+        top = ((1 << 24) - 1) // (n - 1)
+        w = rng.choice([-1, 1], size=(m, u.size)) * rng.integers(top // 2, top + 1, size=(m, u.size))
+        first = u == 0
+        total = np.abs(w[0][first]).sum()
+        w[0, 0] += np.sign(w[0, 0]) * ((1 << 24) - (largest == "edge") - total)
+        assert np.abs(w[0][first]).sum() == (1 << 24) - (largest == "edge")
+    else:
+        # few large weights per row, so that the rows' sums stay below 2^24 where that is possible
+        w = rng.integers(-3, 4, size=(m, u.size))
+        w[:, 0] = -largest
+        w[:, -1] = largest
+    inst = wl.Instance(n, m, u.astype(np.int32), v.astype(np.int32), w.astype(np.int32))
+    p = q.problem_from_instance(inst)
+    c = torch.from_numpy(wl.dirichlet_weights(W, m, 17)).cuda()
+    out = []
+    for path in ("dense_staged", "dense"):
+        s = q.make_schedule("dsb", steps=25, dt=0.5, noise_alpha=alpha, seed=29, path=path)
+        spins, obj, ws, tr = q.qaia_sample_trace(p, c, R, s, 25)
+        torch.cuda.synchronize()
+        out.append([t.cpu().numpy() for t in (spins, obj, tr)])
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
+    assert np.array_equal(out[0][1], oracle.cut_values(inst, unpack_spins(out[0][0], n)))
