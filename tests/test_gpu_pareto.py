@@ -243,3 +243,13 @@ def test_filter_long_lists_by_chunks(q, m, bits):
     pool = np.concatenate([lower, front, front[:77]])
     want = 20_000 + np.arange(40_000) if m > 1 else np.array([20_000 + int(np.argmax(a))])
     assert np.array_equal(_filter(q, pool), want)
+
+
+@pytest.mark.parametrize("M,m", [(1023, 1), (341, 3), (342, 3), (37449, 7), (100001, 5)])
+def test_objective_min_of_flat_ranges(q, M, m):
+    """Threads are a multiple of m: one and several blocks whose last threads are
+    left out, with the minimum in the last row."""
+    import torch
+    a = np.random.default_rng(M).integers(-2**62, 2**62, size=(M, m))
+    a[-1, m - 1] = -2**62 - 1
+    assert np.array_equal(q.qaia_objective_min(torch.from_numpy(a).cuda()).cpu().numpy(), a.min(axis=0))
