@@ -23,8 +23,10 @@
 // or above the diagonal are visited.  The epilogue multiplies by the row spins
 // (one operation per element, shared by the slices, and one per slice) and adds
 // the digits to int64 sums in LDS.  570 000 samples of a complete 200-node graph,
-// m = 3, 19 900 edges: 4.37 ms walking the edges, 0.23 ms here (matrix cores 29 %
-// busy, vector units 35 %); 4096 samples at 2048 nodes: 5.06 and 0.10 ms.
+// m = 3, 19 900 edges: 4.37 ms walking the edges, 0.20 ms here (matrix cores 29 %
+// busy, vector units 30 %; 0.23 ms with an item's first A tiles and row spins
+// read when it begins); 4096 samples at 2048 nodes: 5.06 and 0.10 ms.  Two column
+// tiles per wave and four waves per SIMD instead: 0.31 ms.
 #include <algorithm>
 #include <type_traits>
 
@@ -95,68 +97,79 @@ __global__ __launch_bounds__(kB, 2) void cut_kernel(CutArgs a) {
     const int g0 = kc * kChunkTiles, g1 = min(T, g0 + kChunkTiles);  // the chunk's spin tiles
     const int64_t col0 = (int64_t)blockIdx.x * kCols;
     unsigned long long *q = (unsigned long long *)lds;  // [m][kCols]
-    i32x4 *bs = (i32x4 *)(lds + (size_t)a.m * kCols * 8);  // [chunk tile][column tile][lane]
+    uint32_t *words = (uint32_t *)(q + a.m * kCols);       // [chunk tile][kCols]: the spins as they came
+    i32x4 *bs = (i32x4 *)(words + (g1 - g0) * kCols);      // [chunk tile][column tile][lane]
     for (int i = threadIdx.x; i < a.m * kCols; i += kB) q[i] = 0ull;
     for (int f = wave; f < (g1 - g0) * 4; f += kB / 64) {
         const int64_t col = col0 + (f & 3) * 32 + lr;
-        const uint32_t w = col < a.count ? a.spins[col * a.words2 + g0 + (f >> 2)] >> (16 * half) : 0u;
+        const uint32_t w = col < a.count ? a.spins[col * a.words2 + g0 + (f >> 2)] : 0u;
+        if (half == 0) words[(f >> 2) * kCols + (f & 3) * 32 + lr] = w;
         i32x4 b;
 #pragma unroll
-        for (int d = 0; d < 4; ++d) b[d] = spins4((w >> (4 * d)) & 15u);
+        for (int d = 0; d < 4; ++d) b[d] = spins4(__builtin_amdgcn_ubfe(w, 16 * half + 4 * d, 4));
         bs[f * 64 + lane] = b;
     }
     __syncthreads();
     const bool one = a.L == kGroup;
     const int rows = min(T, g1);  // row tiles with something on or above the diagonal
-    // items (row tile, group) in row-major order, every (4 parts)-th one
-    int r = (part * 4 + wave) / G, grp = (part * 4 + wave) - r * G;
-    const int step_r = 4 * a.parts / G, step_g = 4 * a.parts - step_r * G;
-    for (; r < rows; r += step_r, grp += step_g) {
-        if (grp >= G) {
-            grp -= G;
-            if (++r >= rows) break;
-        }
-        const int s0 = grp * kGroup, ns = min(kGroup, S - s0);
-        const int k0 = max(r, g0);
-        // this lane's columns' spins of the row tile
-        uint32_t rw[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int64_t col = col0 + c * 32 + lr;
-            rw[c] = col < a.count ? a.spins[col * a.words2 + r] >> (4 * half) : 0u;
-        }
-        const i32x4 *src[kGroup];
-#pragma unroll
-        for (int s = 0; s < kGroup; ++s)  // (a missing slice reads the last one; its sums are dropped)
-            src[s] = (const i32x4 *)(a.img + ((int64_t)(s0 + min(s, ns - 1)) * T + r) * T * 1024) + lane;
-        i32x4 av[kGroup], bv[4];
+    // Items (row tile, group) in row-major order, every (4 parts)-th one.  One loop
+    // over all their tiles: an item's last tile loads the first A tiles of the
+    // wave's next item, which arrive behind the sums.
+    const int step = 4 * a.parts, items = rows * G;
+    int item = part * 4 + wave;
+    if (item < items) {
+        int r = item / G, grp = item - r * G, g = max(r, g0);
+        i32x4 av[kGroup];
         i32x16 acc[kGroup][4];
-        // one spin tile: its MFMAs behind the next tile's A loads
-        auto tile = [&](int g, auto first) __attribute__((always_inline)) {
-            i32x4 nx[kGroup];
-            const int gn = min(g + 1, g1 - 1);
-#pragma unroll
-            for (int s = 0; s < kGroup; ++s) nx[s] = src[s][(int64_t)gn * 64];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) bv[c] = bs[((g - g0) * 4 + c) * 64 + lane];
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-#pragma unroll
-                for (int s = 0; s < kGroup; ++s) {
-                    i32x16 zero = {};
-                    acc[s][c] = __builtin_amdgcn_mfma_i32_32x32x32_i8(av[s], bv[c], decltype(first)::value ? zero : acc[s][c],
-                                                                     0, 0, 0);
-                }
-#pragma unroll
-            for (int s = 0; s < kGroup; ++s) av[s] = nx[s];
+        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)a.img, 0, S * T * T * 1024, 0x00027000);
+        auto load = [&](int s, int rr, int gg, int g) __attribute__((always_inline)) {
+            // (a missing slice reads the last one; its sums are dropped)
+            const int at = ((min(gg * kGroup + s, S - 1) * T + rr) * T + g) * 1024;
+            return __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, at, 0));
         };
 #pragma unroll
-        for (int s = 0; s < kGroup; ++s) av[s] = src[s][(int64_t)k0 * 64];
-        tile(k0, std::true_type{});
+        for (int s = 0; s < kGroup; ++s) {
+            av[s] = load(s, r, grp, g);
+            asm volatile("" : "+v"(av[s]));  // arrived: otherwise the loop's first use would wait for its own loads
+        }
+        bool first = true;
+        for (;;) {
+            const bool last = g + 1 == g1;
+            const int ni = last && item + step < items ? item + step : item;
+            const int nr = ni / G, ng = last ? max(nr, g0) : g + 1;
+            i32x4 bv[4];
 #pragma unroll
-        for (int s = 0; s < kGroup; ++s)
-            asm volatile("" : "+v"(av[s]));  // opaque: the compiler would sink the prefetch to the point of use
-        for (int g = k0 + 1; g < g1; ++g) tile(g, std::false_type{});
+            for (int c = 0; c < 4; ++c) bv[c] = bs[((g - g0) * 4 + c) * 64 + lane];
+            // each A tile is replaced as soon as its MFMAs are under way
+            auto tile = [&](auto zero) __attribute__((always_inline)) {
+#pragma unroll
+                for (int s = 0; s < kGroup; ++s) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        i32x16 z = {};
+                        acc[s][c] = __builtin_amdgcn_mfma_i32_32x32x32_i8(av[s], bv[c], decltype(zero)::value ? z : acc[s][c],
+                                                                         0, 0, 0);
+                    }
+                    av[s] = load(s, nr, ni - nr * G, ng);
+                    __builtin_amdgcn_sched_barrier(0x7);
+                }
+            };
+            if (first) tile(std::true_type{});
+            else tile(std::false_type{});
+            if (last) {
+                const int s0 = grp * kGroup, ns = min(kGroup, S - s0);
+                // this lane's columns' spins of the row tile
+                uint32_t rw[4];
+                if (r >= g0) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) rw[c] = words[(r - g0) * kCols + c * 32 + lr] >> (4 * half);
+                } else {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const int64_t col = min(col0 + c * 32 + lr, a.count - 1);
+                        rw[c] = a.spins[col * a.words2 + r] >> (4 * half);
+                    }
+                }
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             // -x = ~x + 1: the row signs as an exclusive or (one v_xad per slice), the ones added at the end
@@ -181,6 +194,14 @@ __global__ __launch_bounds__(kB, 2) void cut_kernel(CutArgs a) {
                     const int k = (s0 + s) / a.L, l = s0 + s - k * a.L;
                     atomicAdd(qc + k * kCols, (unsigned long long)((int64_t)sum[s] << (8 * l)));
                 }
+        }
+                if (ni == item) break;
+                item = ni;
+                r = nr;
+                grp = ni - nr * G;
+            }
+            first = last;
+            g = ng;
         }
     }
     __syncthreads();
@@ -267,7 +288,7 @@ void launch_cut(const Problem &p, const uint64_t *spins, int64_t count, int64_t 
     // about 1024 blocks where there are too few samples to fill the GPU, four items (one per wave) each at least
     const int64_t most = std::max<int64_t>(1, (int64_t)std::min(c.T, kChunkTiles) * G / 4);
     const int parts = (int)std::min<int64_t>(most, std::max<int64_t>(1, 1024 / (bx * chunks)));
-    const size_t shmem = (size_t)p.m * kCols * 8 + (size_t)std::min(c.T, kChunkTiles) * 4096;
+    const size_t shmem = (size_t)p.m * kCols * 8 + (size_t)std::min(c.T, kChunkTiles) * (4096 + kCols * 4);
     const CutArgs a{(const uint32_t *)spins, count, 2 * p.words, p.m, c.L, c.T, parts, c.img, c.total, obj};
     const dim3 grid((unsigned)bx, (unsigned)(chunks * parts));
     if (chunks * parts == 1) {
