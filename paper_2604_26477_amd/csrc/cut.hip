@@ -267,7 +267,6 @@ void cut_build(Problem &p) {
     hipLaunchKernelGGL(cut_image_kernel, dim3((unsigned)((n + kB - 1) / kB)), dim3(kB), 0, nullptr, p.d_eu, p.d_ev, p.d_W,
                        p.E, p.m, L, (int)T, c.img);
     QAIA_HIP(hipGetLastError());
-    QAIA_HIP(hipStreamSynchronize(nullptr));
     c.T = (int)T;
     c.L = L;
     c.ok = true;

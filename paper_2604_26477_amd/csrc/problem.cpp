@@ -155,6 +155,7 @@ Problem *build_problem(int32_t n, int32_t m, int64_t E, const int32_t *eu, const
         dense_build(*p);
         resident_build(*p);
         cut_build(*p);
+        QAIA_HIP(hipStreamSynchronize(nullptr));  // the images are complete for every stream
         jit_prepare(*p);
     } catch (...) {
         delete p;

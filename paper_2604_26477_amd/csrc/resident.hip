@@ -568,7 +568,6 @@ void resident_build(Problem &p) {
     if (d.digits)
         hipLaunchKernelGGL(digit_kernel, blocks(ed), dim3(kB), 0, nullptr, d.J32, p.m, d.Np, p.n, d.digits, d.FD);
     QAIA_HIP(hipGetLastError());
-    QAIA_HIP(hipStreamSynchronize(nullptr));
 }
 
 void resident_release(Problem &p) {

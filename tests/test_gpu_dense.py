@@ -354,3 +354,30 @@ def test_exact_digits_equal_register_tiles_bitwise(q, n, W, R, largest, alpha):
     for a, b in zip(*out):
         assert np.array_equal(a, b)
     assert np.array_equal(out[0][1], oracle.cut_values(inst, unpack_spins(out[0][0], n)))
+
+
+@pytest.mark.parametrize("largest,frac", [(1, 0), (255, 0), (448, 0), (449, 4), (262143, 16), (2**31 - 1, 16)])
+def test_image_rounding(q, largest, frac):
+    """The reduced images' values, read off as the field of disjoint edges: ties,
+    subnormals, every binade and both signs, against the host's conversions of
+    the scaled weights."""
+    import torch
+    rng = np.random.default_rng(largest % 997)
+    mags = [largest] + [largest >> s for s in range(1, 31)] + [(3 * largest) >> (s + 1) for s in range(1, 30)]
+    mags += [(17 << s) >> 1 for s in range(0, 27)] + [(257 << s) >> 1 for s in range(0, 22)]
+    mags += rng.integers(0, largest + 1, 150).tolist()
+    w = np.array([x for x in mags if 0 <= x <= largest], np.int64)
+    w[1::2] *= -1
+    n = 2 * w.size
+    inst = wl.Instance(n, 1, np.arange(0, n, 2, dtype=np.int32), np.arange(1, n, 2, dtype=np.int32),
+                       w.astype(np.int32)[None], frac)
+    p = q.problem_from_instance(inst)
+    phi = torch.ones((1, n), device="cuda")
+    e16 = int(np.floor(np.log2(largest))) - 7
+    e8 = int(np.ceil(np.log2(largest / 448.0)))
+    e8 += int(largest * 2.0**-e8 > 448)
+    v16 = torch.from_numpy(w * 2.0**-e16).float().to(torch.bfloat16).double() * 2.0**e16
+    v8 = torch.from_numpy(w * 2.0**-e8).float().to(torch.float8_e4m3fn).double() * 2.0**e8
+    for prec, want in (("bf16", v16), ("fp8", v8), ("fp32", torch.from_numpy(w).float().double())):
+        got = q.qaia_dense_field(p, prec, phi).cpu().double()[0, 0]
+        assert torch.equal(got[0::2], want) and torch.equal(got[1::2], want), prec
