@@ -1156,12 +1156,12 @@ FLayout filter_layout(int64_t M, int32_t m) {
     L.pruned = take(4 * Mz);
     L.fin = take(4 * Mz);
     L.dom = take(Mz);
-    L.packed = take(4 * Mz * (size_t)std::min(std::max(m, 1), 8));
     // a power of two of at least 1.5 M slots (load factor <= 2/3)
     uint64_t c = 1024;
     while (c < (uint64_t)Mz + Mz / 2) c <<= 1;
     L.table_slots = c;
-    L.table = take(4 * c);
+    // the offsets are written once the table's slots have been collected
+    L.table = L.packed = take(std::max<size_t>(4 * c, 4 * Mz * (size_t)std::min(std::max(m, 1), 8)));
     L.total_bytes = off;
     return L;
 }
