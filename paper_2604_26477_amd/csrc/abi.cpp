@@ -76,8 +76,13 @@ int plan_path(const Problem &p, const qaia_schedule &s, bool tracing) {
 // lane, same bits: 42 nodes x 3200 replicas 76 / 31 us, x 20 000 77 / 63, x 40 000
 // 81 / 108; 20 nodes x 10 000 44 / 36, x 20 000 45 / 48; 12 nodes x 3200 35 / 32,
 // x 10 000 34 / 36; with noise 42 nodes x 3200 510 / 66, x 40 000 540 / 437.
+// Past degree 3 a group's neighbour reads grow and the line comes sooner: 50 nodes
+// of 8 % density x 6400 115 / 100, x 10 000 113 / 117; complete 16 nodes x 6400
+// 146 / 60; complete 12 nodes x 192 48 / 53; with noise complete 20 nodes x 25 000
+// 326 / 239, x 40 000 336 / 350.
 bool few_replicas(const Problem &p, int64_t rows, bool noise) {
-    return rows <= (noise ? 40000 : p.n >= 20 ? 16384 : 4096);
+    if (p.max_degree <= 3) return rows <= (noise ? 40000 : p.n >= 20 ? 16384 : 4096);
+    return rows <= (noise ? 25000 : p.n >= 16 ? 6400 : 0);
 }
 
 WsLayout full_layout(const Problem &p, int64_t W, int32_t R, const qaia_schedule &s, int path) {

@@ -487,3 +487,21 @@ def test_automatic_choice_of_few_replicas(q, n, m, W, R, variant, alpha):
         assert q.qaia_workspace_status(ws) == 0
         out.append((spins, obj))
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("n,kind,W,R", [(12, "complete", 3, 64), (16, "complete", 400, 16), (16, "complete", 6401, 1),
+                                        (20, "p0.5", 100, 250), (20, "p0.5", 100, 251), (50, "p0.08", 64, 100)])
+@pytest.mark.parametrize("variant,alpha", [("bsb", 0.0), ("dsb", 0.1)])
+def test_automatic_choice_past_degree_three(q, n, kind, W, R, variant, alpha):
+    """Past degree 3 the limits are 6400 replicas from 16 nodes and 25 000 with
+    noise: both sides equal the generated kernel bit for bit."""
+    import torch
+    p = q.problem_from_instance(wl.random_instance(n, 3, kind, seed=3100 + n))
+    c = torch.from_numpy(wl.dirichlet_weights(W, 3, 3200 + n)).cuda()
+    out = []
+    for path in ("auto", "sparse_reg"):
+        s = q.make_schedule(variant, steps=21, dt=0.5, noise_alpha=alpha, seed=43, path=path)
+        spins, obj, ws = q.qaia_sample(p, c, R, s)
+        torch.cuda.synchronize()
+        out.append((spins, obj))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
