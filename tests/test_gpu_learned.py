@@ -313,3 +313,19 @@ def test_backward_split_and_whole_tiles(q, D, B):
     want = omlp.backward(vals, X.astype(np.float64), y.astype(np.float64), D)
     scale = _grad_magnitude(vals, X.astype(np.float64), y.astype(np.float64), D)
     assert (np.abs(got - want) <= 1e-3 * np.abs(want) + 1e-5 * scale).all()
+
+
+@pytest.mark.parametrize("m,P", [(3, 341), (3, 342), (7, 146), (7, 147), (6, 2731), (1, 1025)])
+def test_features_of_fronts_in_flat_ranges(q, m, P):
+    """The range is read by a multiple of m threads (1023 of 1024 at m = 3) and the
+    front divided by several blocks: extremes in the first and the last rows, one
+    objective without a range; tolerance of test_features_at_tile_edges."""
+    rng = np.random.default_rng(P)
+    front = rng.integers(-10**6, 10**7, size=(P, m)).astype(np.int64)
+    front[0] = -2 * 10**6
+    front[-1] = 2 * 10**7
+    front[:, m - 1] = front[:, m - 1] if m == 1 else 5
+    cands, hits, misses = (rng.dirichlet(np.ones(m), size=k).astype(np.float32).reshape(k, m) for k in (70, 3, 4))
+    got = q.qaia_front_features(_dev(front), _dev(cands), _dev(hits), _dev(misses)).cpu().numpy()
+    want = omlp.features(front, cands.astype(np.float64), hits.astype(np.float64), misses.astype(np.float64))
+    np.testing.assert_allclose(got[:, m:], want, rtol=0, atol=2e-5)
