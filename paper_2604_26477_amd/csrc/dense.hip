@@ -121,13 +121,54 @@ __device__ __forceinline__ void mma_tile(const void *Jv, const void *phiv, int N
     }
 }
 
-// One step for the tile (bx, by) of a job; MT accumulator tiles, j.m <= MT.
-template <int PREC, int MT, bool DSB>
+// The FP32 product of a thin tile's wave: 32 spins x 32 columns of M objectives.
+// The fragments of 128 bytes per row (whole requests) come straight from global
+// memory into one of two register sets, while the other one's MFMAs run; the
+// k-groups go in increasing order as everywhere.
+template <int M>
+__device__ __forceinline__ void thin_mma(const void *Jv, const void *phiv, int Np_, int row_w, int col_w, int half,
+                                         int lr, f16v (&acc)[M][1]) {
+    constexpr int KG = 8, G = 4;
+    const size_t Np = (size_t)Np_;
+    const float *arow = (const float *)Jv + (size_t)(row_w + lr) * Np + half * (KG / 2);
+    const float *bcol = (const float *)phiv + (size_t)(col_w + lr) * Np + half * (KG / 2);
+    f32x4 a[2][M][G], b[2][G];
+    auto load = [&](int s, int k0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+#pragma unroll
+            for (int k = 0; k < M; ++k) a[s][k][g] = *(const f32x4 *)(arow + (size_t)k * Np * Np + k0 + g * KG);
+            b[s][g] = *(const f32x4 *)(bcol + k0 + g * KG);
+        }
+        __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of the other set's MFMAs
+    };
+    auto mul = [&](int s) __attribute__((always_inline)) {
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int k = 0; k < M; ++k)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    acc[k][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s][k][g][e], b[s][g][e], acc[k][0], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    load(0, 0);
+    for (int k0 = 0; k0 < Np_; k0 += 2 * G * KG) {  // Np is a multiple of 128
+        load(1, k0 + G * KG);
+        mul(0);
+        load(0, k0 + 2 * G * KG < Np_ ? k0 + 2 * G * KG : k0);
+        mul(1);
+    }
+}
+
+// One step for the tile (bx, by) of a job; MT accumulator tiles, j.m <= MT; CB
+// blocks of 32 columns per wave (1: the thin tile, j.m = MT).
+template <int PREC, int MT, bool DSB, int CB = 2>
 __device__ __forceinline__ void dense_step_body(const DenseJob &j, int t, int bx, int by) {
     const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int half = l >> 5, lr = l & 31;
     const int row_w = by * kTileM + (wv & 1) * 32;
-    const int col_w = bx * kTileN + (wv >> 1) * 64;
+    const int col_w = bx * CB * 64 + (wv >> 1) * CB * 32;
     constexpr int M = MT;
     const int m = j.m;
     // discrete SB: x in place, Phi double-buffered; ballistic SB: x double-buffered, Phi = x
@@ -136,19 +177,20 @@ __device__ __forceinline__ void dense_step_body(const DenseJob &j, int t, int bx
     float *x_out = DSB ? j.xa : (even ? j.xb : j.xa);
     const void *phi_in = DSB ? (even ? j.pa : j.pb) : (const void *)x_in;
     void *phi_out = DSB ? (even ? j.pb : j.pa) : nullptr;
-    f16v acc[M][2];
+    f16v acc[M][CB];
 #pragma unroll
     for (int k = 0; k < M; ++k)
 #pragma unroll
-        for (int cb = 0; cb < 2; ++cb)
+        for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[k][cb][i] = 0.0f;
-    mma_tile<PREC, M>(j.J, phi_in, j.Np, m, row_w, col_w, half, lr, acc);
+    if constexpr (CB == 1) thin_mma<M>(j.J, phi_in, j.Np, row_w, col_w, half, lr, acc);
+    else mma_tile<PREC, M>(j.J, phi_in, j.Np, m, row_w, col_w, half, lr, acc);
 
     const float kt = j.kt_tab[t];
     const size_t Np = (size_t)j.Np;
 #pragma unroll
-    for (int cb = 0; cb < 2; ++cb) {
+    for (int cb = 0; cb < CB; ++cb) {
         const int col = col_w + cb * 32 + lr;
         float cf[M];
 #pragma unroll
@@ -207,6 +249,11 @@ __device__ __forceinline__ void dense_step_body(const DenseJob &j, int t, int bx
 template <int PREC, int M, bool DSB>
 __global__ __launch_bounds__(kDB) void dense_step_kernel(DenseJob j, int t) {
     dense_step_body<PREC, M, DSB>(j, t, blockIdx.x, blockIdx.y);
+}
+
+template <int M, bool DSB>
+__global__ __launch_bounds__(kDB) void dense_thin_kernel(DenseJob j, int t) {
+    dense_step_body<QAIA_FP32, M, DSB, 1>(j, t, blockIdx.x, blockIdx.y);
 }
 
 // Grouped step over a ragged batch of dense jobs (each with its own n, m,
@@ -1261,9 +1308,23 @@ static int device_cus() {
     return cus;
 }
 
+// FP32 steps whose thin tiles (64 x 64, four of a wave's 32 x 32 each) are at most
+// two per CU take them instead of the staged ones: a step then lasts one wave's chain of
+// MFMAs, which is a quarter as long.  Staged against thin, us per step: N = 1024,
+// m = 3, 600 columns (160 thin tiles) 189 / 74, 2048 columns (512) 191 / 160; N = 2048,
+// 256 columns (128) 368 / 132, 600 (320) 370 / 312, 1200 (608) 372 / 472.  BF16 and FP8,
+// whose MFMAs are short beside the loads, lose (N = 1024, 600 columns 26 / 36, 17 / 23).
+static bool dense_thin(int64_t tiles_x, int64_t tiles_y) { return 4 * tiles_x * tiles_y <= 2 * device_cus(); }
+
 template <int PREC, int M, bool DSB>
 static void staged_launch(dim3 grid, hipStream_t st, const DenseJob &j, int t) {
     constexpr int NW = staged_waves<PREC>();
+    if constexpr (PREC == QAIA_FP32) {
+        if (dense_thin(grid.x, grid.y)) {
+            hipLaunchKernelGGL((dense_thin_kernel<M, DSB>), dim3(2 * grid.x, 2 * grid.y), dim3(kDB), 0, st, j, t);
+            return;
+        }
+    }
     if constexpr (staged_wide<PREC, M>()) {
         if ((j.tiles_x % 2) == 0 && (int64_t)(j.tiles_x / 2) * j.tiles_y >= device_cus()) {
             hipLaunchKernelGGL((dense_step_staged_kernel<PREC, M, DSB, NW, 4>), dim3(grid.x / 2, grid.y), dim3(64 * NW),
@@ -1423,7 +1484,15 @@ void launch_dense(const Problem &p, const float *weights, int64_t W, int32_t R,
     const int64_t cols = W * (int64_t)R;
     if (cols == 0) return;
     QAIA_CHECK(L.colsP <= INT32_MAX / 2, QAIA_INVALID_ARGUMENT, "too many replicas for the dense path");
-    if (staged && resident_fits(p)) {
+    // Few columns of more than 256 spins: a resident block's many waves share their SIMDs'
+    // matrix cores, the thin tiles spread over the chip (one per CU), which is worth the
+    // launches.  Resident against thin, us per step: 512 spins, m = 4, up to 2048 columns
+    // 116 / 53-57, 4096 116 / 113; 400 spins, m = 3, 2048 columns 68 / 39, 4096 68 / 83;
+    // 300 spins, m = 2 27 / 22; 256 spins, m = 4 31 / 31; 200 spins, m = 3 19 / 22.
+    const bool digits = s.variant == QAIA_DSB && p.dense.digits > 0;
+    const bool thin = s.precision == QAIA_FP32 && p.n > 256 && !digits &&
+                      4 * (L.colsP / kT2) * (p.dense.Np / kT2) <= device_cus();
+    if (staged && resident_fits(p) && !thin) {
         launch_resident(p, weights, W, R, s, ws, L, spins, trace, trace_steps, st);
         launch_evaluate(p, spins, cols, obj, st);
         return;

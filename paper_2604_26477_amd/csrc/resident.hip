@@ -19,7 +19,8 @@
 //
 // Bound by the FP32 matrix rate where columns fill the GPU (512 spins, m = 4, 8192
 // columns: 117 us per step of 111 at the rate a large product reaches, 135 staged),
-// with few columns by one block's chain of MFMAs.  Per step, staged -> here:
+// with few columns by one block's chain of MFMAs (past 256 spins such calls take the
+// thin tiles of dense.hip instead, its launch_dense says where).  Per step, staged -> here:
 // n = 256, m = 3, 8192 columns 56 -> 26, BF16 15.0 -> 5.2, FP8 12.4 -> 3.5; n = 70,
 // m = 4, 200 columns 40 -> 5.7 (the launches).  512 spins are sixteen waves; past
 // that a wave would need two row tiles and their registers.

@@ -381,3 +381,14 @@ def test_image_rounding(q, largest, frac):
     for prec, want in (("bf16", v16), ("fp8", v8), ("fp32", torch.from_numpy(w).float().double())):
         got = q.qaia_dense_field(p, prec, phi).cpu().double()[0, 0]
         assert torch.equal(got[0::2], want) and torch.equal(got[1::2], want), prec
+
+
+@pytest.mark.parametrize("n,m,W,R", [(257, 1, 3, 50), (300, 2, 1, 2049), (384, 3, 5, 27), (512, 4, 2, 1024), (512, 1, 1, 2049),
+                                     (640, 2, 13, 99), (700, 4, 1, 1), (1030, 3, 7, 9)])
+@pytest.mark.parametrize("variant,alpha", [("bsb", 0.0), ("dsb", 0.0), ("bsb", 0.2), ("dsb", 0.1)])
+def test_thin_tiles_equal_register_tiles_bitwise(q, n, m, W, R, variant, alpha):
+    """FP32 with few columns: steps of 64 x 64 tiles, on both sides of one and
+    two tiles per CU, ragged columns and padded rows."""
+    _, (a, b) = _both_tiles(q, n, m, W, R, 9, variant, "fp32", alpha)
+    for x, y in zip(a, b):
+        assert np.array_equal(x, y)
