@@ -14,9 +14,9 @@
 //   - branch B: dense items are set up, then each of the T steps is ONE launch
 //     of the grouped dense step kernel over the tiles of all dense items, then
 //     each dense item is read out and evaluated;
-//   - branches A, C and D in turn: the staged dense items that fit the resident
-//     kernel (all steps in one launch), each a launch of its own, since a small
-//     item holds few CUs;
+//   - the staged dense items that fit the resident kernel (all steps in one
+//     launch) take it instead where few or large items make that the shorter way
+//     (resident_pays): a launch each, dealt to branches A, C and D;
 //   - the branches join and the caller's stream waits for the graph.
 // The kernel families differ in their tile shape and replicas per wave: one
 // replica per lane (64 replicas per wave, generated kernel), one spin per
@@ -24,6 +24,7 @@
 // tile knob: more replicas per block put several spins on each lane, generic
 // kernel), or 64- / 128-spin x 128-replica matrix-core tiles (dense kernels).
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <vector>
 
@@ -50,6 +51,7 @@ struct ItemPlan {
     int path;
     WsLayout L;
     size_t base;  // offset of the item's region in the batch workspace
+    bool resident = false;  // a launch of its own for all steps, not part of the grouped steps
 };
 
 int default_path(const Problem &p, const qaia_schedule &s) {
@@ -86,8 +88,72 @@ void check_tile(const Problem &p, int path, int tile, int64_t rows) {
     (void)sparse_lds_shape(p, std::max<int64_t>(rows, 1), tile);  // throws past 16 spins per lane
 }
 
-bool is_resident(const ItemPlan &ip) { return ip.path == QAIA_PATH_DENSE_STAGED && resident_fits(*ip.p); }
-bool is_grouped_dense(const ItemPlan &ip) { return is_dense_path(ip.path) && !is_resident(ip); }
+bool may_be_resident(const ItemPlan &ip) { return ip.path == QAIA_PATH_DENSE_STAGED && resident_fits(*ip.p); }
+bool is_grouped_dense(const ItemPlan &ip) { return is_dense_path(ip.path) && !ip.resident; }
+
+// Estimates for the choice below, us per step, with constants fitted to 30 .. 512
+// spins, m = 2 .. 4, most within 20 %.
+constexpr double kChipCUs = 256.0;
+
+// One block (32 columns) of the resident kernels: its MFMA chain, as many waves as
+// share a SIMD in sequence.  FP32 512 spins, m = 4: 116 us, 256 spins 31, 70 spins
+// 6.1; BF16 16, 5.5, 2.7; exact digits (discrete SB) 256 spins 6.8, 70 spins 2.4.
+double resident_block_us(const Problem &p, const qaia_schedule &s, int64_t *blocks, int64_t cols) {
+    const int tiles = (p.n + 31) / 32, per_block = tiles >= 3 ? 1 : 4 / tiles;
+    *blocks = (cols + 32 * per_block - 1) / (32 * per_block);
+    const double deep = (double)((tiles * per_block + 3) / 4) * p.m;
+    if (s.precision == QAIA_BF16) return 1.7 + 0.027 * deep * ((p.n + 15) / 16);
+    if (s.precision == QAIA_FP8) return 1.7 + 0.07 * deep * ((p.n + 63) / 64);
+    if (s.variant == QAIA_DSB && p.dense.digits > 0) return 1.4 + 0.028 * deep * tiles * p.dense.digits;
+    return 1.7 + 0.113 * deep * ((p.n + 7) / 8);
+}
+
+// One tile of the grouped step: FP32 512 spins, m = 4: 130 us, 256 spins 72, 128
+// spins, m = 2 27; BF16 21, 16, 12.
+double staged_tile_us(const Problem &p, const qaia_schedule &s) {
+    const double work = (double)p.dense.Np * p.m;
+    if (s.precision == QAIA_FP32) return 10.0 + 0.059 * work;
+    return 11.0 + (s.precision == QAIA_BF16 ? 0.0048 : 0.0035) * work;
+}
+
+// Whether the items that may be resident take a launch each or join the grouped
+// steps.  The launches run three at a time, so many items of few columns leave most
+// of the chip idle: 48 items of 512 spins, m = 4, 64 columns in FP32 take 1872 us per
+// step as launches and 276 grouped, 6 of them 235 and 133, 3 of them 117 and 131;
+// 48 of 4096 columns 2803 and 3189.  BF16 256, 57; 33, 23; 17, 21; 456, 751.  Small
+// graphs pay with more of them (70 spins, m = 4, 64 columns: 24 items 50 and 51),
+// exact digits nearly always (48 items of 256 spins, m = 4, 64 columns 109 and 158).  An
+// item's share of the launches' time is a third of its block's while its blocks are
+// few, more where blocks of two launches meet on a CU and both are bound by the matrix
+// cores (FP32 products of at most eight waves), and its share of the chip once they
+// fill it.  The grouped step's tiles run one per CU, in whole rounds.
+bool resident_pays(const std::vector<ItemPlan> &items, const qaia_batch_item *its, const qaia_schedule &s) {
+    double launches = 0.0, grouped = 0.0;
+    double chain[5] = {}, work[5] = {};  // grouped step per m: its longest tile, all its tiles
+    int64_t slots[5] = {};
+    for (size_t i = 0; i < items.size(); ++i) {
+        const ItemPlan &ip = items[i];
+        const int64_t cols = its[i].W * (int64_t)its[i].R;
+        if (ip.path != QAIA_PATH_DENSE_STAGED || cols == 0) continue;
+        const Problem &p = *ip.p;
+        const double tile = staged_tile_us(p, s);
+        const int64_t tiles = (((cols + 127) / 128) * (p.dense.Np / 128) + 7) / 8 * 8;
+        chain[p.m] = std::max(chain[p.m], tile);
+        work[p.m] += tile * (double)tiles;
+        slots[p.m] += tiles;
+        if (!resident_fits(p)) continue;
+        int64_t blocks = 0;
+        const double block = resident_block_us(p, s, &blocks, cols);
+        const bool fp32 = s.precision == QAIA_FP32 && !(s.variant == QAIA_DSB && p.dense.digits > 0);
+        const double share = (double)blocks / kChipCUs;
+        const double few = !fp32 || p.n > 256 ? 0.36 : std::min(1.0 / 3 + share * 4 / 3, p.n > 128 ? 0.53 : 0.75);
+        launches += block * std::max(fp32 ? share : 1.2 * share, few);
+    }
+    for (int m = 1; m <= 4; ++m)
+        if (slots[m] > 0)
+            grouped += std::max(chain[m], work[m] / (double)slots[m] * std::ceil((double)slots[m] / kChipCUs));
+    return launches <= grouped;
+}
 
 struct BatchLayout {
     std::vector<ItemPlan> items;
@@ -112,13 +178,15 @@ BatchLayout batch_layout(const qaia_batch_item *items, int32_t count, const qaia
         ItemPlan ip{&p, path, sample_ws_layout(p, it.W, it.R, s, !is_dense_path(path)), off};
         if (is_dense_path(path)) {
             dense_ws_extend(p, it.W, it.R, s, ip.L);
-            if (is_grouped_dense(ip)) ++B.n_dense;
+            ++B.n_dense;
         } else if (path == QAIA_PATH_SPARSE_LDS) {
             ++B.n_sparse;
         }
         off += align256(ip.L.total);
         B.items.push_back(ip);
     }
+    if (resident_pays(B.items, items, s))
+        for (ItemPlan &ip : B.items) ip.resident = may_be_resident(ip);
     B.jobs_off = off;
     off += align256(sizeof(SparseJob) * (size_t)std::max(B.n_sparse, 1));
     off += align256(sizeof(DenseJob) * (size_t)std::max(B.n_dense, 1));
@@ -333,17 +401,20 @@ void sample_batch(const qaia_batch_item *items, int32_t count, const qaia_schedu
         for (int i = 0, turn = 0; i < count; ++i) {
             const ItemPlan &ip = B.items[i];
             const qaia_batch_item &it = items[i];
-            if (!is_resident(ip) || it.W * it.R == 0) continue;
+            if (!ip.resident || it.W * it.R == 0) continue;
             const int d = turn++ % 3;
             if (d > 0 && turn <= 3) QAIA_HIP(hipStreamWaitEvent(deal[d], ev_fork, 0));
-            launch_dense(*ip.p, it.weights, it.W, it.R, s, base + ip.base, ip.L, it.spins, it.obj, nullptr, 0, true,
-                         deal[d]);
+            // (not through launch_dense, whose thin tiles are a launch per step)
+            launch_resident(*ip.p, it.weights, it.W, it.R, s, base + ip.base, ip.L, it.spins, nullptr, 0, deal[d]);
+            launch_evaluate(*ip.p, it.spins, it.W * (int64_t)it.R, it.obj, deal[d]);
             forked = std::max(forked, d);
         }
         QAIA_HIP(hipEventRecord(ev_join, ps.b));
         for (int d = 1; d <= forked; ++d) QAIA_HIP(hipEventRecord(ev_side[d - 1], deal[d]));
         // branch B: dense items
-        if (B.n_dense > 0) {
+        bool any_grouped = false;
+        for (const auto &v : djobs) any_grouped |= !v.empty();
+        if (any_grouped) {
             int di[kGroups] = {0, 0, 0, 0, 0};
             for (int i = 0; i < count; ++i) {
                 const ItemPlan &ip = B.items[i];

@@ -211,3 +211,36 @@ def test_tile_knob_rejected_where_it_does_not_apply(q):
     with pytest.raises(q.QaiaError) as e:  # 100 replicas x 42 spins > 16 spins per lane
         q.qaia_sample_batch([q.BatchItem(p, c, 4, "sparse_lds", tile=100)], s)
     assert e.value.status == q.QAIA_UNSUPPORTED
+
+
+def _batch_equals_per_item_calls(q, specs, variant, prec, alpha, T):
+    import torch
+    s = q.make_schedule(variant, precision=prec, steps=T, dt=0.5, noise_alpha=alpha, seed=101, replica_offset=3)
+    one = q.make_schedule(variant, precision=prec, steps=T, dt=0.5, noise_alpha=alpha, seed=101, replica_offset=3,
+                          path="dense")
+    items, refs = [], []
+    for i, (n, m, kind, W, R) in enumerate(specs):
+        p = q.problem_from_instance(wl.random_instance(n, m, kind, seed=1400 + i))
+        c = _dev(wl.dirichlet_weights(W, m, 1500 + i)) if W else torch.zeros((0, m), dtype=torch.float32, device="cuda")
+        items.append(q.BatchItem(p, c, R, "dense_staged"))
+        refs.append(q.qaia_sample(p, c, R, one)[:2])
+    ws = None
+    for _ in range(2):
+        for it in items:
+            it.spins.fill_(-1)
+            it.obj.fill_(-1)
+        ws = q.qaia_sample_batch(items, s, workspace=ws)
+        torch.cuda.synchronize()
+        for spec, it, (sp, ob) in zip(specs, items, refs):
+            assert torch.equal(it.spins, sp) and torch.equal(it.obj, ob), spec
+
+
+@pytest.mark.parametrize("count", [1, 3, 24])
+@pytest.mark.parametrize("variant,prec,alpha", [("bsb", "fp32", 0.0), ("dsb", "fp32", 0.1), ("dsb", "bf16", 0.0),
+                                                ("dsb", "fp8", 0.0)])
+def test_batch_of_staged_items_up_to_512_nodes(q, count, variant, prec, alpha):
+    """Few such items are a launch each, many of few columns join the grouped
+    steps: the same bits as the register tiles, ragged sizes in every m group."""
+    sizes = [(512, 4), (300, 2), (257, 1), (130, 3), (70, 4), (31, 2), (384, 3), (200, 1)]
+    specs = [(*sizes[i % len(sizes)], "p0.3", 1 + i % 3, 5 + i % 7) for i in range(count)]
+    _batch_equals_per_item_calls(q, specs, variant, prec, alpha, 12)

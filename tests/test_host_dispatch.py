@@ -1,0 +1,148 @@
+"""Which kernels the library's host side launches, without a GPU: libqaia in a
+process of its own on a HIP runtime of host memory (fake_hip.cpp), which notes
+the launches by name."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PRELUDE = """
+import ctypes as C
+import sys
+import numpy as np
+fake = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+lib = C.CDLL(sys.argv[2])
+fake.fake_limit.argtypes = [C.c_size_t]
+fake.fake_in_use.restype = C.c_size_t
+lib.qaia_last_error.restype = C.c_char_p
+
+
+class Schedule(C.Structure):
+    _fields_ = [("variant", C.c_int32), ("precision", C.c_int32), ("steps", C.c_int32), ("path", C.c_int32),
+                ("dt", C.c_float), ("a0", C.c_float), ("init_amp", C.c_float), ("noise_alpha", C.c_float),
+                ("seed", C.c_uint64), ("replica_offset", C.c_uint64)]
+
+
+class Item(C.Structure):
+    _fields_ = [("problem", C.c_void_p), ("weights", C.c_void_p), ("W", C.c_int64), ("R", C.c_int32),
+                ("path", C.c_int32), ("spins", C.c_void_p), ("obj", C.c_void_p), ("tile", C.c_int32),
+                ("reserved", C.c_int32)]
+
+
+def ok(rc):
+    assert rc == 0, (rc, lib.qaia_last_error())
+
+
+def ptr(a):
+    return a.ctypes.data_as(C.c_void_p)
+
+
+def count(name):
+    return fake.fake_count(name.encode())
+
+
+def edges(n, density, seed=1):
+    u, v = np.triu_indices(n, 1)
+    keep = np.random.default_rng(seed).random(u.size) < density
+    return u[keep].astype(np.int32), v[keep].astype(np.int32)
+
+
+def ring(n):
+    u = np.arange(n - 1, dtype=np.int32)
+    return u, u + 1
+
+
+def problem(n, m, u, v, largest):
+    w = np.random.default_rng(n).integers(-largest, largest + 1, size=(m, u.size)).astype(np.int32)
+    p = C.c_void_p()
+    ok(lib.qaia_problem_create(n, m, C.c_int64(u.size), ptr(u), ptr(v), ptr(w), 16, 0, C.byref(p)))
+    return p
+
+
+def buffers(n, m, rows):
+    return np.zeros((rows, (n + 63) // 64), np.int64), np.zeros((rows, m), np.int64)
+
+
+def sample(p, n, m, W, R, s):
+    c, (spins, obj), need = np.full((W, m), 1.0 / m, np.float32), buffers(n, m, W * R), C.c_size_t()
+    ok(lib.qaia_sample_workspace_bytes(p, C.c_int64(W), R, C.byref(s), C.byref(need)))
+    ws = np.zeros(need.value, np.uint8)
+    fake.fake_clear()
+    ok(lib.qaia_sample(p, ptr(c), C.c_int64(W), R, C.byref(s), ptr(spins), ptr(obj), ptr(ws), need, None))
+
+
+def batch(items, s):
+    # items: (problem, n, m, W, R)
+    keep, arr = [], (Item * len(items))()
+    for a, (p, n, m, W, R) in zip(arr, items):
+        c, (spins, obj) = np.full((W, m), 1.0 / m, np.float32), buffers(n, m, W * R)
+        keep += [c, spins, obj]
+        a.problem, a.weights, a.W, a.R, a.path = p, c.ctypes.data, W, R, 4
+        a.spins, a.obj = spins.ctypes.data, obj.ctypes.data
+    need = C.c_size_t()
+    ok(lib.qaia_sample_batch_workspace_bytes(arr, len(items), C.byref(s), C.byref(need)))
+    ws = np.zeros(need.value, np.uint8)
+    fake.fake_clear()
+    ok(lib.qaia_sample_batch(arr, len(items), C.byref(s), ptr(ws), need, None))
+
+
+BSB, DSB, FP32, BF16, FP8 = 0, 1, 0, 1, 2
+AUTO, SPARSE_REG, SPARSE_LDS, DENSE, STAGED = range(5)
+SMALL, LARGE = 1000, 1 << 22  # weights whose rows stay below 2^24 (exact digits), and not
+"""
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    lib = os.path.join(ROOT, "paper_2604_26477_amd", "libqaia.so")
+    so = str(tmp_path_factory.mktemp("fake") / "libfakehip.so")
+    subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-std=c++17", "-o", so, os.path.join(ROOT, "tests", "fake_hip.cpp")],
+                   check=True)
+
+    def go(body, *args):
+        env = dict(os.environ, QAIA_DISABLE_JIT="1")
+        r = subprocess.run([sys.executable, "-c", PRELUDE + textwrap.dedent(body), so, lib, *map(str, args)],
+                           capture_output=True, text=True, env=env, timeout=300)
+        assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-4000:]
+    return go
+
+
+# ---------------------------------------------------------------- batch
+
+@pytest.mark.parametrize("n,items,W,R,variant,precision,largest,grouped", [
+    (300, 30, 8, 8, "BSB", "FP32", "LARGE", True),   # many, few columns: one grouped launch per step
+    (512, 48, 32, 32, "BSB", "FP32", "LARGE", True),
+    (512, 24, 8, 8, "DSB", "BF16", "LARGE", True),
+    (512, 3, 8, 8, "BSB", "FP32", "LARGE", False),   # as many as there are branches
+    (300, 1, 8, 8, "BSB", "FP32", "LARGE", False),
+    (400, 24, 64, 64, "BSB", "FP32", "LARGE", False),  # each fills much of the chip
+    (70, 48, 8, 8, "DSB", "FP32", "SMALL", False),   # exact digits
+])
+def test_batch_of_staged_items_takes_the_shorter_way(run, n, items, W, R, variant, precision, largest, grouped):
+    """Staged items of up to 512 spins are a launch each only where that is the
+    shorter way; never a launch per item and step (the thin tiles of single calls)."""
+    run("""
+    n, k, W, R, grouped = (int(x) for x in sys.argv[3:8])
+    m, T = 2, 40
+    s = Schedule(%s, %s, T, AUTO, 0.5, 1.0, 0.1, 0.0, 1, 0)
+    p = problem(n, m, *edges(n, 0.3), %s)
+    batch([(p, n, m, W, R)] * k, s)
+    one = count("resident_kernel") + count("digits_kernel")
+    steps = count("dense_batch_step_staged")
+    assert count("dense_thin") == 0 and count("dense_step") == 0
+    assert (one, steps) == ((0, T) if grouped else (k, 0)), (one, steps)
+    """ % (variant, precision, largest), n, items, W, R, int(grouped))
+
+
+def test_batch_of_small_and_large_staged_items(run):
+    """Items past 512 spins stay in the grouped steps, whatever the others take."""
+    run("""
+    s = Schedule(BSB, FP32, 20, AUTO, 0.5, 1.0, 0.1, 0.0, 1, 0)
+    big, small = problem(600, 3, *edges(600, 0.1), LARGE), problem(64, 3, *edges(64, 0.5), LARGE)
+    batch([(big, 600, 3, 8, 8), (small, 64, 3, 8, 8), (small, 64, 3, 0, 8)], s)
+    assert count("dense_batch_step_staged") == 20 and count("resident_kernel") == 1
+    """)
