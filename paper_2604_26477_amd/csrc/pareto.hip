@@ -21,10 +21,13 @@
 //    drop dominated rows, and every dominated row keeps a dominator (a front
 //    vector above it is never dropped), so the rest has the pool's front.
 // 3. Packing.  The listed vectors as 32-bit offsets from the first one, in
-//    list order; offsets that do not fit raise a flag.
+//    list order; offsets that do not fit raise a flag.  A list that is still
+//    longer than kPairMax is laid out by falling value of a monotone key in
+//    kBuckets steps, so that a row's dominators stand before the end of its step.
 // 4. Pairs.  Every pair of 256-row tiles is one work item of a persistent
 //    grid: a row is marked when another row is >= it componentwise (the
-//    vectors are distinct, so that is dominance).
+//    vectors are distinct, so that is dominance).  Of an ordered list only the
+//    tiles before the end of the row's step are compared.
 // 5. The unmarked rows' sample indices go into a bitmap over 0..M-1 and are
 //    emitted in ascending order.
 // Nothing is sorted: a sort by objective costs three launches per digit, all
@@ -472,15 +475,37 @@ struct PairList {
     __device__ __forceinline__ const int32_t *list(int r) const { return r == 0 ? all : r == 1 ? pruned : chunked; }
 };
 
+// The bucket of a row in an ordered list, the largest keys first.  The key is a sum
+// of the normalised values with falling weights (equal ones would put a front of
+// constant sum into one bucket); every operation is monotone in floating point too,
+// so a row's dominators lie in its bucket or an earlier one.
+constexpr int kBuckets = 512;
+template <int MM>
+__device__ __forceinline__ int key_bucket(const int64_t (&y)[MM], const int64_t *__restrict__ lo,
+                                          const int64_t *__restrict__ hi) {
+    float key = 0.0f, w = 1.0f, top = 0.0f;
+#pragma unroll
+    for (int k = 0; k < MM; ++k) {
+        const double span = (double)hi[k] - (double)lo[k];
+        const float scale = span > 0.0 ? (float)(1.0 / span) : 0.0f;
+        key = fmaf(w, (float)(((double)y[k] - (double)lo[k]) * scale), key);
+        top += w;
+        w *= 0.70710678f;
+    }
+    return kBuckets - 1 - (int)fminf(fmaxf(key * ((float)kBuckets / top), 0.0f), (float)(kBuckets - 1));
+}
+
 // Chunk pass over a long pruned list, in any order: a row that another row of
 // its chunk of 1024 dominates is dropped, the others are appended.  Each thread
 // holds four rows in registers and walks the chunk once for all four (one
 // broadcast LDS read of a row serves four comparisons), stopping when all four
-// are dominated.
+// are dominated.  hist counts the rows left per bucket.
 template <int MM>
 __global__ __launch_bounds__(kB) void chunk_any_kernel(const int64_t *__restrict__ obj,
                                                        const int32_t *__restrict__ list, const int64_t *counts,
-                                                       int32_t *__restrict__ out, int64_t *out_count) {
+                                                       const int64_t *__restrict__ lo, const int64_t *__restrict__ hi,
+                                                       int32_t *__restrict__ out, int64_t *out_count,
+                                                       uint32_t *__restrict__ hist) {
     constexpr int RPT = kChunk / kB;  // rows per thread
     __shared__ int64_t v[kChunk][MM];
     const int64_t n = counts[1];
@@ -522,6 +547,7 @@ __global__ __launch_bounds__(kB) void chunk_any_kernel(const int64_t *__restrict
             const int j = r * kB + threadIdx.x;
             const bool left = j < len && !dom[r];
             wave_append(left, left ? list[c0 + j] : 0, out, out_count);
+            if (left) atomicAdd(&hist[key_bucket<MM>(y[r], lo, hi)], 1u);
         }
         __syncthreads();  // v is rewritten by the next chunk
     }
@@ -529,15 +555,34 @@ __global__ __launch_bounds__(kB) void chunk_any_kernel(const int64_t *__restrict
 
 // fin[i] = the i-th listed row, packed[i] = its vector as 32-bit offsets from
 // the first listed row's, dom[i] = 0; counts[3] = the list's length, counts[4]
-// = 1 when some offset does not fit.
+// = 1 when some offset does not fit.  An ordered list (route 2): row i is the next
+// one of its bucket (hist: rows per bucket, taken: rows placed so far), and
+// limit[t] = where the bucket of tile t's last row ends.
 template <int MM>
 __global__ __launch_bounds__(kB) void pair_pack_kernel(const int64_t *__restrict__ obj, PairList L, int64_t *counts,
-                                                       int32_t *__restrict__ fin, int32_t *__restrict__ packed,
-                                                       uint8_t *__restrict__ dom) {
+                                                       const int64_t *__restrict__ lo, const int64_t *__restrict__ hi,
+                                                       const uint32_t *__restrict__ hist, uint32_t *__restrict__ taken,
+                                                       int32_t *__restrict__ limit, int32_t *__restrict__ fin,
+                                                       int32_t *__restrict__ packed, uint8_t *__restrict__ dom) {
+    __shared__ uint32_t end[kBuckets], part[kB];
     const int route = L.route();
     const int64_t n = L.counts[route];
     if (blockIdx.x == 0 && threadIdx.x == 0) counts[3] = n;
     if (n == 0) return;
+    if (route == 2) {  // inclusive sums of hist, two buckets per thread
+        const uint32_t c0 = hist[2 * threadIdx.x], c1 = hist[2 * threadIdx.x + 1];
+        part[threadIdx.x] = c0 + c1;
+        __syncthreads();
+        for (int off = 1; off < kB; off <<= 1) {
+            const uint32_t o = (int)threadIdx.x >= off ? part[threadIdx.x - off] : 0u;
+            __syncthreads();
+            part[threadIdx.x] += o;
+            __syncthreads();
+        }
+        end[2 * threadIdx.x + 1] = part[threadIdx.x];
+        end[2 * threadIdx.x] = part[threadIdx.x] - c1;
+        __syncthreads();
+    }
     int64_t base[MM];
     const int32_t *list = L.list(route);
     const int64_t r0 = list[0];
@@ -546,14 +591,22 @@ __global__ __launch_bounds__(kB) void pair_pack_kernel(const int64_t *__restrict
     bool wide = false;
     for (int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x; i < n; i += (int64_t)gridDim.x * kB) {
         const int64_t r = list[i];
-        fin[i] = (int32_t)r;
-        dom[i] = 0;
+        int64_t y[MM];
+#pragma unroll
+        for (int k = 0; k < MM; ++k) y[k] = obj[r * MM + k];
+        int64_t p = i;
+        if (route == 2) {
+            const int b = key_bucket<MM>(y, lo, hi);
+            p = (int64_t)(b > 0 ? end[b - 1] : 0u) + atomicAdd(&taken[b], 1u);
+            if (p % kB == kB - 1 || p == n - 1) limit[p / kB] = (int32_t)end[b];
+        }
+        fin[p] = (int32_t)r;
+        dom[p] = 0;
 #pragma unroll
         for (int k = 0; k < MM; ++k) {
-            const int64_t y = obj[r * MM + k];
-            const uint64_t mag = y >= base[k] ? (uint64_t)y - (uint64_t)base[k] : (uint64_t)base[k] - (uint64_t)y;
+            const uint64_t mag = y[k] >= base[k] ? (uint64_t)y[k] - (uint64_t)base[k] : (uint64_t)base[k] - (uint64_t)y[k];
             wide |= mag > 0x3fffffffull;  // differences of two offsets fit 32 bits
-            packed[i * MM + k] = (int32_t)((uint64_t)y - (uint64_t)base[k]);
+            packed[p * MM + k] = (int32_t)((uint64_t)y[k] - (uint64_t)base[k]);
         }
     }
     if (__ballot(wide) != 0 && (threadIdx.x & 63) == 0)
@@ -570,11 +623,19 @@ __global__ __launch_bounds__(kB) void pair_pack_kernel(const int64_t *__restrict
 // rows marked by the first tiles skip the later ones: a wave whose rows are all
 // marked stops.  Concurrent marks all store the same byte.  The 64-bit form,
 // for ranges past 32 bits, stages the rows i in LDS.
+// An ordered list halves the pairs and puts the rows that dominate most first: a
+// front of 600 000 points of two objectives 66 -> 39 ms, of eight with 64-bit
+// differences 338 -> 108, 2 000 000 rows on forty nested fronts of eight 571 -> 182.
+// hist and taken lie at the start of the bitmap of kept rows (cleared, if given).
 template <int MM>
 __global__ __launch_bounds__(kB) void pair_any_kernel(const int64_t *__restrict__ obj, const int64_t *__restrict__ counts,
+                                                      const int32_t *__restrict__ limit, uint32_t *__restrict__ cleared,
                                                       const int32_t *__restrict__ fin,
                                                       const int32_t *__restrict__ packed, uint8_t *dom) {
+    if (cleared != nullptr && blockIdx.x == 0)
+        for (int i = threadIdx.x; i < 2 * kBuckets; i += kB) cleared[i] = 0u;
     const int64_t n = counts[3];
+    const bool ordered = counts[0] > kPairMax && counts[1] > kPairMax;
     const bool wide = counts[4] != 0;
     const int64_t T = (n + kB - 1) / kB;
     // rows i per item: all 256, fewer where the list alone would not fill the
@@ -591,6 +652,7 @@ __global__ __launch_bounds__(kB) void pair_any_kernel(const int64_t *__restrict_
             if (++it >= TI) break;
         }
         const int64_t i0 = it * isz;
+        if (ordered && i0 >= limit[jt]) continue;
         const int64_t j = jt * kB + threadIdx.x;
         bool done = j >= n || dom[j] != 0;
         const int cnt = (int)((n - i0) < isz ? (n - i0) : isz);
@@ -637,12 +699,15 @@ __global__ __launch_bounds__(kB) void pair_any_kernel(const int64_t *__restrict_
                 int64_t yj[MM];
 #pragma unroll
                 for (int k = 0; k < MM; ++k) yj[k] = y[k];
-                for (int t = 0; t < cnt && !hit; ++t) {
-                    bool ge = !diag || t != self;
+                for (int t0 = 0; t0 < cnt && !hit; t0 += 4)
 #pragma unroll
-                    for (int k = 0; k < MM; ++k) ge &= v[t][k] >= yj[k];
-                    hit = ge;
-                }
+                    for (int u = 0; u < 4; ++u) {
+                        const int t = min(t0 + u, cnt - 1);
+                        bool ge = !diag || t != self;
+#pragma unroll
+                        for (int k = 0; k < MM; ++k) ge &= v[t][k] >= yj[k];
+                        hit |= ge;
+                    }
             }
             __syncthreads();  // v is rewritten by the next item
         }
@@ -1264,7 +1329,7 @@ void launch_filter(const int64_t *obj, int64_t M, int64_t *keep_idx, int64_t *nu
     const bool small = M <= kEmitSmall;
     hipLaunchKernelGGL(filter_init_kernel, dim3((unsigned)std::min<int64_t>(grid_for((int64_t)L.table_slots / 4), 2048)),
                        dim3(kB), 0, st, (int4 *)table, (int64_t)L.table_slots / 4, (uint32_t *)bits,
-                       small ? 0 : 2 * L.words, counts, best, lo, hi);
+                       M > kPairMax ? 2 * L.words : 0, counts, best, lo, hi);
     hipLaunchKernelGGL(dedupe_kernel<MM>, dim3((unsigned)std::min<int64_t>(grid_for(M, kDedupRows), 4096)), dim3(kDT),
                        0, st, obj, M, table, (uint32_t)(L.table_slots - 1));
     hipLaunchKernelGGL(collect_kernel, dim3((unsigned)std::min<int64_t>(grid_for((int64_t)L.table_slots, 16 * kB), kCollectBlocks)),
@@ -1273,6 +1338,11 @@ void launch_filter(const int64_t *obj, int64_t M, int64_t *keep_idx, int64_t *nu
     const RowList distinct{all, counts + 0, 0};
     // the chunk survivors reuse the distinct list's memory: by then only the pruned list is read
     int32_t *chunked = all;
+    // an ordered list's counters take the start of the bitmap, which the marks need later; its limits
+    // the pruned list's memory
+    uint32_t *hist = M > kPairMax ? (uint32_t *)bits : nullptr;
+    static_assert(kPairMax / 8 >= 8 * kBuckets, "both counters fit the bitmap of more than kPairMax rows");
+    int32_t *limit = pruned;
     if (M > kPairMax) {
         const int64_t sample = std::min<int64_t>(M, kSampleRows);
         hipLaunchKernelGGL((sample_range_kernel<MM, true>), dim3((unsigned)std::min<int64_t>(grid_for(sample), 512)),
@@ -1282,13 +1352,14 @@ void launch_filter(const int64_t *obj, int64_t M, int64_t *keep_idx, int64_t *nu
         hipLaunchKernelGGL(prune_kernel<MM>, dim3((unsigned)std::min<int64_t>(grid_for(M, 64), 2048)), dim3(kB), 0, st,
                            obj, distinct, best, pruned, counts + 1);
         hipLaunchKernelGGL(chunk_any_kernel<MM>, dim3((unsigned)std::min<int64_t>(grid_for(M, kChunk), 4096)), dim3(kB),
-                           0, st, obj, pruned, counts, chunked, counts + 2);
+                           0, st, obj, pruned, counts, lo, hi, chunked, counts + 2, hist);
     }
     hipLaunchKernelGGL(pair_pack_kernel<MM>, dim3((unsigned)std::min<int64_t>(grid_for(M), 1024)), dim3(kB), 0, st, obj,
-                       PairList{all, pruned, chunked, counts}, counts, fin, packed, dom);
+                       PairList{all, pruned, chunked, counts}, counts, lo, hi, hist,
+                       hist ? hist + kBuckets : nullptr, limit, fin, packed, dom);
     const int64_t tiles = grid_for(M);
     hipLaunchKernelGGL(pair_any_kernel<MM>, dim3((unsigned)std::min<int64_t>(tiles * tiles * 8, kPairBlocks)), dim3(kB), 0,
-                       st, obj, counts, fin, packed, dom);
+                       st, obj, counts, limit, hist, fin, packed, dom);
     if (small) {
         hipLaunchKernelGGL(emit_small_kernel, dim3(1), dim3(1024), 0, st, fin, dom, counts, keep_idx, num_keep);
     } else {

@@ -253,3 +253,28 @@ def test_objective_min_of_flat_ranges(q, M, m):
     a = np.random.default_rng(M).integers(-2**62, 2**62, size=(M, m))
     a[-1, m - 1] = -2**62 - 1
     assert np.array_equal(q.qaia_objective_min(torch.from_numpy(a).cuda()).cpu().numpy(), a.min(axis=0))
+
+
+@pytest.mark.parametrize("front,lower,m,bits,outliers", [
+    (32769, 0, 2, 16, False), (33024, 300, 3, 16, False), (40000, 25536, 2, 36, False), (40000, 25537, 4, 16, False),
+    (66000, 1, 2, 16, True), (70001, 40000, 8, 40, True), (140000, 100000, 3, 20, True), (150000, 9, 1, 20, False)])
+def test_filter_long_lists_in_key_order(q, front, lower, m, bits, outliers):
+    """Lists that stay longer than 32 768 rows are laid out by a monotone key: at the
+    shortest such list, whole and ragged tiles, pools on both sides of the one-block
+    emission (65 536 rows), both forms of the pairs, dominated rows on forty nested
+    fronts, duplicates, and two rows so far out that all others share a step."""
+    rng = np.random.default_rng(front + lower)
+    a = rng.permutation(front).astype(np.int64) << (bits - 16)
+    if outliers:
+        a[:2] = (1 << 61, -(1 << 61))
+    rows = np.stack([a * (-1) ** k + k for k in range(m)], axis=1)
+    below = rows[rng.integers(0, front, lower)] - (rng.integers(1, 40, (lower, 1)) << (bits - 16))
+    below -= rng.integers(0, 3, below.shape)
+    pool = np.concatenate([rows, below, rows[:50]])
+    order = rng.permutation(len(pool))
+    where = np.argsort(order)  # pool row i stands at where[i]
+    best = np.arange(front) if m > 1 else np.array([np.argmax(a)])
+    first = where[best]
+    twin = best < 50
+    first[twin] = np.minimum(first[twin], where[front + lower + best[twin]])
+    assert np.array_equal(_filter(q, pool[order]), np.sort(first))
