@@ -291,16 +291,17 @@ __global__ __launch_bounds__(kB) void filter_init_kernel(int4 *__restrict__ tabl
     }
 }
 
-// 32-bit hash of a vector: one multiply per objective (its two words folded
-// first) and a final mix.  32-bit multiplies issue at a quarter of the rate,
-// 64-bit ones take three of them.
+// 32-bit hash of a vector: a multiply for each of the two words of an objective
+// and a final mix (32-bit multiplies issue at a quarter of the rate, 64-bit ones
+// take three of them).  The words have multipliers of their own: folded by a rotation
+// they cancelled for values that repeat their low word in the high one, and all
+// vectors of such a pool met in one slot.
 template <int MM>
 __device__ __forceinline__ uint32_t vec_hash(const int64_t (&y)[MM]) {
     uint32_t h = 0x243F6A88u;
 #pragma unroll
     for (int k = 0; k < MM; ++k) {
-        const uint32_t lo = (uint32_t)y[k], hi = (uint32_t)((uint64_t)y[k] >> 32);
-        h = (h ^ lo ^ ((hi << 13) | (hi >> 19))) * 0x9E3779B1u;
+        h = (h ^ (uint32_t)y[k]) * 0x9E3779B1u + (uint32_t)((uint64_t)y[k] >> 32) * 0xC2B2AE3Du;
         h ^= h >> 15;
     }
     h *= 0x85EBCA77u;

@@ -278,3 +278,28 @@ def test_filter_long_lists_in_key_order(q, front, lower, m, bits, outliers):
     twin = best < 50
     first[twin] = np.minimum(first[twin], where[front + lower + best[twin]])
     assert np.array_equal(_filter(q, pool[order]), np.sort(first))
+
+
+def test_filter_of_values_that_repeat_their_words(q):
+    """Values whose low and high words hold the same pattern spread over the hash
+    tables like any others: 20 000 of them take the time of random ones (all in one
+    slot, each would walk past all earlier ones: hundreds of times as long)."""
+    import torch
+    rng = np.random.default_rng(5)
+    k = rng.permutation(20_000).astype(np.int64)
+    pools = [np.stack([v, -v], axis=1) for v in (k * (2**32 + 2**13), k * 2**20 + rng.integers(0, 2**20, k.size))]
+    took = []
+    for pool in pools:
+        t = torch.from_numpy(pool).cuda()
+        ws = torch.empty(q.qaia_pareto_filter_workspace_bytes(*pool.shape), dtype=torch.uint8, device="cuda")
+        best = float("inf")
+        for _ in range(4):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            _, num, _ = q.qaia_pareto_filter(t, workspace=ws)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        assert int(num.item()) == k.size
+        took.append(best)
+    assert took[0] < 10 * took[1], took
