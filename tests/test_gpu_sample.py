@@ -505,3 +505,29 @@ def test_automatic_choice_past_degree_three(q, n, kind, W, R, variant, alpha):
         torch.cuda.synchronize()
         out.append((spins, obj))
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("n,kind,m,W,R", [
+    (1, "deg3", 3, 70, 1), (2, "complete", 8, 3, 5), (2, "complete", 1, 33, 1), (3, "complete", 4, 257, 3), (5, "complete", 8, 7, 9),
+    (7, "deg3", 2, 65, 1), (12, "deg3", 3, 41, 2), (12, "complete", 8, 31, 4), (20, "deg3", 3, 22, 1), (21, "p0.2", 1, 9, 4),
+    (32, "deg3", 8, 3, 1), (32, "complete", 8, 5, 3), (8, "deg3", 3, 700, 101), (32, "deg3", 5, 400, 42)])
+@pytest.mark.parametrize("alpha", [0.0, 0.2])
+def test_read_out_of_several_groups_in_a_wave(q, n, kind, m, W, R, alpha):
+    """Small graphs share a wave: few edges are walked by a lane per replica and
+    objective, more by the whole wave, also where the last block holds fewer groups
+    and where groups of four replicas are ragged.  Against the batch form's tiled
+    kernel, with an invalid weight row."""
+    import torch
+    inst = wl.random_instance(n, m, kind, seed=3300 + n) if n > 1 else wl.Instance(
+        1, m, np.zeros(0, np.int32), np.zeros(0, np.int32), np.zeros((m, 0), np.int32))
+    p = q.problem_from_instance(inst)
+    w = wl.dirichlet_weights(W, m, 3400 + n)
+    w[W // 2] = 0.0
+    c = torch.from_numpy(w).cuda()
+    s = q.make_schedule("bsb", steps=23, dt=0.5, noise_alpha=alpha, seed=47, replica_offset=2, path="sparse_lds")
+    spins, obj, _ = q.qaia_sample(p, c, R, s)
+    item = q.BatchItem(p, c, R, "sparse_lds")
+    q.qaia_sample_batch([item], s)
+    torch.cuda.synchronize()
+    assert torch.equal(spins, item.spins) and torch.equal(obj, item.obj)
+    assert not obj[W // 2 * R:(W // 2 + 1) * R].any()
