@@ -80,9 +80,19 @@ int plan_path(const Problem &p, const qaia_schedule &s, bool tracing) {
 // of 8 % density x 6400 115 / 100, x 10 000 113 / 117; complete 16 nodes x 6400
 // 146 / 60; complete 12 nodes x 192 48 / 53; with noise complete 20 nodes x 25 000
 // 326 / 239, x 40 000 336 / 350.
-bool few_replicas(const Problem &p, int64_t rows, bool noise) {
-    if (p.max_degree <= 3) return rows <= (noise ? 40000 : p.n >= 20 ? 16384 : 4096);
-    return rows <= (noise ? 25000 : p.n >= 16 ? 6400 : 0);
+// Short runs do not pay for a group's longer set-up and read-out, which grow with the
+// replicas, all the less the fewer nodes the generated chain has.  Whole calls: 42
+// nodes x 256, 5 steps 20 / 20 us, 20 steps 24 / 20; 12 nodes x 256, 200 steps 54 / 39;
+// 2 nodes x 3200, 200 steps 25 / 32; 24 nodes x 16 000, 40 steps 26 / 33, 200 steps
+// 86 / 84; with noise 70 nodes x 40 000, 5 steps 59 / 87, 20 steps 184 / 181; complete
+// 18 nodes x 25 000, 20 steps 64 / 79, 40 steps 116 / 113; 2 nodes x 256, 40 steps
+// 20 / 21.  The read-out takes the objectives in turn: more steps past four of them.
+bool few_replicas(const Problem &p, int64_t rows, int32_t steps, bool noise) {
+    const bool degree3 = p.max_degree <= 3;
+    const int64_t n = p.n, T = steps, paid = p.m > 4 ? T * 2 / 3 : T;
+    if (noise) return rows <= (degree3 ? 40000 : 25000) && paid * n >= 80 && T * (degree3 ? 1500 : 1000) >= rows;
+    if (rows > (degree3 ? (n >= 20 ? 16384 : 4096) : n >= 16 ? 6400 : 0)) return false;
+    return paid * n * n >= (degree3 ? 8000 : 4000) && T * (degree3 ? 250 : 300) >= rows;
 }
 
 WsLayout full_layout(const Problem &p, int64_t W, int32_t R, const qaia_schedule &s, int path) {
@@ -138,7 +148,7 @@ int32_t sample_impl(const qaia_problem *pp, const float *weights, int64_t W, int
     else if (path == QAIA_PATH_SPARSE_REG) {
         const bool noise = s->dt * s->noise_alpha != 0.0f;
         if (s->path == QAIA_PATH_AUTO && s->precision == QAIA_FP32 && trace_steps == 0 && sparse_group_fits(p) &&
-            few_replicas(p, rows, noise)) {
+            few_replicas(p, rows, s->steps, noise)) {
             // the generated noise kernel is still built by the first call, for the calls that need it built
             if (noise) jit_ensure(p, s->variant, true);
             launch_sparse_group(p, W, R, *s, ws, L, spins, obj, nullptr, 0, st);

@@ -90,8 +90,8 @@ int hipEventSynchronize(void *) { return 0; }
 int hipEventQuery(void *) { return 0; }
 int hipEventElapsedTime(float *ms, void *, void *) { return *ms = 1.0f, 0; }
 int hipEventDestroy(void *) { return 0; }
-int hipModuleLoadData(void **, const void *) { return 1; }
-int hipModuleGetFunction(void **, void *, const char *) { return 1; }
+int hipModuleLoadData(void **m, const void *) { return *m = malloc(1), 0; }
+int hipModuleGetFunction(void **f, void *, const char *) { return *f = malloc(1), 0; }
 int hipModuleUnload(void *) { return 0; }
 int hipModuleLaunchKernel(void *, unsigned, unsigned, unsigned, unsigned, unsigned, unsigned, unsigned, void *, void **,
                           void **) { return launched.push_back("generated"), 0; }

@@ -531,3 +531,21 @@ def test_read_out_of_several_groups_in_a_wave(q, n, kind, m, W, R, alpha):
     torch.cuda.synchronize()
     assert torch.equal(spins, item.spins) and torch.equal(obj, item.obj)
     assert not obj[W // 2 * R:(W // 2 + 1) * R].any()
+
+
+@pytest.mark.parametrize("n,m,W,R,steps", [(12, 2, 256, 16, 56), (12, 2, 256, 16, 55), (20, 3, 1024, 16, 66), (20, 3, 1024, 16, 65),
+                                           (9, 8, 33, 5, 149), (2, 3, 5, 1, 2000)])
+@pytest.mark.parametrize("variant", ["bsb", "dsb"])
+def test_automatic_choice_by_steps(q, n, m, W, R, steps, variant):
+    """Few replicas take one spin per lane only for runs long enough: both sides
+    equal the generated kernel bit for bit."""
+    import torch
+    p = q.problem_from_instance(wl.random_instance(n, m, "deg3" if n > 2 else "complete", seed=3500 + n))
+    c = torch.from_numpy(wl.dirichlet_weights(W, m, 3600 + n)).cuda()
+    out = []
+    for path in ("auto", "sparse_reg"):
+        s = q.make_schedule(variant, steps=steps, dt=0.5, seed=53, path=path)
+        spins, obj, ws = q.qaia_sample(p, c, R, s)
+        torch.cuda.synchronize()
+        out.append((spins, obj))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])

@@ -103,8 +103,10 @@ def run(tmp_path_factory):
     subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-std=c++17", "-o", so, os.path.join(ROOT, "tests", "fake_hip.cpp")],
                    check=True)
 
-    def go(body, *args):
-        env = dict(os.environ, QAIA_DISABLE_JIT="1")
+    def go(body, *args, jit=False):
+        env = {k: v for k, v in os.environ.items() if k != "QAIA_DISABLE_JIT"}
+        if not jit:
+            env["QAIA_DISABLE_JIT"] = "1"
         r = subprocess.run([sys.executable, "-c", PRELUDE + textwrap.dedent(body), so, lib, *map(str, args)],
                            capture_output=True, text=True, env=env, timeout=300)
         assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-4000:]
@@ -146,3 +148,27 @@ def test_batch_of_small_and_large_staged_items(run):
     batch([(big, 600, 3, 8, 8), (small, 64, 3, 8, 8), (small, 64, 3, 0, 8)], s)
     assert count("dense_batch_step_staged") == 20 and count("resident_kernel") == 1
     """)
+
+
+# ---------------------------------------------------------------- single calls
+
+def test_few_replicas_leave_the_generated_kernel_only_for_runs_long_enough(run):
+    """AUTO on a graph of the generated kernel: one spin per lane for few replicas
+    and enough steps for its set-up and read-out, both sides of each line."""
+    run("""
+    cases = [  # n, complete, m, rows, steps, noise, one spin per lane
+        (12, 0, 3, 256, 55, 0.0, 0), (12, 0, 3, 256, 56, 0.0, 1), (12, 0, 3, 4096, 200, 0.0, 1), (12, 0, 3, 4097, 200, 0.0, 0),
+        (2, 0, 3, 64, 1000, 0.0, 0), (42, 0, 4, 1, 4, 0.0, 0), (42, 0, 4, 1, 5, 0.0, 1), (42, 0, 4, 16384, 65, 0.0, 0),
+        (42, 0, 4, 16384, 66, 0.0, 1), (42, 0, 4, 16385, 1000, 0.0, 0), (42, 0, 5, 1, 7, 0.0, 0), (42, 0, 5, 1, 8, 0.0, 1),
+        (16, 1, 3, 64, 15, 0.0, 0), (16, 1, 3, 64, 16, 0.0, 1), (16, 1, 3, 6400, 21, 0.0, 0), (16, 1, 3, 6400, 22, 0.0, 1),
+        (16, 1, 3, 6401, 1000, 0.0, 0), (14, 1, 3, 1, 1000, 0.0, 0),
+        (12, 0, 3, 64, 6, 0.2, 0), (12, 0, 3, 64, 7, 0.2, 1), (12, 0, 3, 40000, 26, 0.2, 0), (12, 0, 3, 40000, 27, 0.2, 1),
+        (12, 0, 3, 40001, 1000, 0.2, 0), (16, 1, 3, 25000, 24, 0.2, 0), (16, 1, 3, 25000, 25, 0.2, 1)]
+    made = {}
+    for n, complete, m, rows, steps, noise, group in cases:
+        key = n, complete, m
+        if key not in made:
+            made[key] = problem(n, m, *(edges(n, 1.1) if complete else ring(n)), SMALL)
+        sample(made[key], n, m, rows, 1, Schedule(BSB, FP32, steps, AUTO, 1.0, 1.0, 0.1, noise, 1, 0))
+        assert (count("group_kernel"), count("generated")) == (group, 1 - group), (n, m, rows, steps, noise)
+    """, jit=True)
