@@ -85,7 +85,7 @@ struct Problem {
     // device images
     int32_t *d_eu = nullptr, *d_ev = nullptr, *d_W = nullptr;
     int32_t *d_rowptr = nullptr, *d_col = nullptr, *d_eid = nullptr;
-    int32_t *d_order = nullptr, *d_place = nullptr;  // nodes by falling degree, and each node's place there
+    int32_t *d_order = nullptr, *d_place = nullptr;  // nodes by falling degree, and each node's place there (group.hip's graphs)
     int64_t *d_rho = nullptr;  // [m][n] row sums sum_j W_k,ij (exact)
     // generated register-resident kernels, index = variant (bSB, dSB)
     JitKernel *jit[2] = {nullptr, nullptr};
@@ -185,7 +185,7 @@ void launch_prep(const Problem &p, const float *weights, int64_t W, const qaia_s
 void launch_sparse_lds(const Problem &p, int64_t W, int32_t R, const qaia_schedule &s, void *ws,
                        const WsLayout &L, uint64_t *spins, int64_t *obj, float *trace,
                        int32_t trace_steps, hipStream_t st, int rpb = 0);
-// one spin per lane, groups of replicas (group.hip): the generic kernel's graphs of up to 1024 spins and degree 16
+// one spin per lane, groups of replicas (group.hip): the generic kernel's graphs of up to 1024 spins and degree 32
 bool sparse_group_fits(const Problem &p);
 void group_order(const Problem &p, std::vector<int32_t> &order, std::vector<int32_t> &place);
 void launch_sparse_group(const Problem &p, int64_t W, int32_t R, const qaia_schedule &s, void *ws, const WsLayout &L,

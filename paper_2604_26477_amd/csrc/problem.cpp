@@ -148,10 +148,12 @@ Problem *build_problem(int32_t n, int32_t m, int64_t E, const int32_t *eu, const
         p->d_col = upload(p->col);
         p->d_eid = upload(p->eid);
         p->d_rho = upload(rho);
-        std::vector<int32_t> order, place;
-        group_order(*p, order, place);
-        p->d_order = upload(order);
-        p->d_place = upload(place);
+        if (sparse_group_fits(*p)) {
+            std::vector<int32_t> order, place;
+            group_order(*p, order, place);
+            p->d_order = upload(order);
+            p->d_place = upload(place);
+        }
         dense_build(*p);
         resident_build(*p);
         cut_build(*p);

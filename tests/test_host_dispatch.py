@@ -172,3 +172,24 @@ def test_few_replicas_leave_the_generated_kernel_only_for_runs_long_enough(run):
         sample(made[key], n, m, rows, 1, Schedule(BSB, FP32, steps, AUTO, 1.0, 1.0, 0.1, noise, 1, 0))
         assert (count("group_kernel"), count("generated")) == (group, 1 - group), (n, m, rows, steps, noise)
     """, jit=True)
+
+
+# ---------------------------------------------------------------- problems
+
+@pytest.mark.parametrize("n,degree,order", [(1024, 2, True), (1025, 2, False), (200, 33, False)])
+def test_only_graphs_of_the_one_spin_per_lane_kernel_get_its_lane_order(run, n, degree, order):
+    """The device memory of a graph without images: its edges, weights, lists and row
+    sums, and the order of that kernel (up to 1024 nodes and degree 32) where it runs."""
+    run("""
+    n, degree, order = (int(x) for x in sys.argv[3:6])
+    m = 8
+    u, v = ring(n)
+    if degree > 2:
+        u, v = np.concatenate([u, np.zeros(degree - 1, np.int32)]), np.concatenate([v, np.arange(2, degree + 1, dtype=np.int32)])
+    E = u.size
+    p = problem(n, m, u, v, SMALL)
+    plain = 4 * (2 * E + m * E + (n + 1) + 4 * E) + 8 * m * n
+    assert fake.fake_in_use() - plain == (8 * n if order else 0), (fake.fake_in_use(), plain)
+    ok(lib.qaia_problem_destroy(p))
+    assert fake.fake_in_use() == 0
+    """, n, degree, int(order))
