@@ -253,13 +253,13 @@ void cut_build(Problem &p) {
     const int64_t bytes = (int64_t)p.m * L * T * T * 1024;
     if (bytes > (int64_t(1) << 29)) return;
     DeviceGuard g(p.device);
-    auto alloc = [](void **q, size_t b) {
-        const hipError_t e = hipMalloc(q, b);
-        if (e == hipErrorOutOfMemory) throw Error{QAIA_OUT_OF_MEMORY, "device allocation failed"};
-        QAIA_HIP(e);
-    };
-    alloc((void **)&c.img, (size_t)bytes);
-    alloc((void **)&c.total, sizeof(int64_t) * (size_t)p.m);
+    // without room for the images the edges are walked
+    if (!try_alloc((void **)&c.img, (size_t)bytes)) return;
+    if (!try_alloc((void **)&c.total, sizeof(int64_t) * (size_t)p.m)) {
+        (void)hipFree(c.img);
+        c.img = nullptr;
+        return;
+    }
     QAIA_HIP(hipMemcpy(c.total, p.total.data(), sizeof(int64_t) * (size_t)p.m, hipMemcpyHostToDevice));
     hipLaunchKernelGGL(cut_zero_kernel, dim3((unsigned)std::min<int64_t>((bytes / 16 + kB - 1) / kB, 4096)), dim3(kB), 0,
                        nullptr, (uint4 *)c.img, bytes / 16);

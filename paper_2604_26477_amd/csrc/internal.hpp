@@ -42,6 +42,18 @@ struct DeviceGuard {
     ~DeviceGuard();
 };
 
+// Device memory for what a problem can do without: false, and no error left behind, where there is no room.
+inline bool try_alloc(void **p, size_t bytes) {
+    const hipError_t e = hipMalloc(p, bytes);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        *p = nullptr;
+        return false;
+    }
+    QAIA_HIP(e);
+    return true;
+}
+
 // ----------------------------------------------------------------- problem
 struct JitKernel;  // generated per-graph kernel (jit.cpp)
 

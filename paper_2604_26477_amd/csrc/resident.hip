@@ -554,9 +554,10 @@ void resident_build(Problem &p) {
     char *b = nullptr;
     d.digits = digits_of(p);
     const int64_t ed = (int64_t)p.m * d.digits * tiles * digit_groups(p.n) * 1024;
-    const hipError_t e = hipMalloc((void **)&b, (size_t)(4 * e32 + 2 * e16 + e8 + ed));  // 1 KB multiples
-    if (e == hipErrorOutOfMemory) throw Error{QAIA_OUT_OF_MEMORY, "device allocation failed"};
-    QAIA_HIP(e);
+    if (!try_alloc((void **)&b, (size_t)(4 * e32 + 2 * e16 + e8 + ed))) {  // 1 KB multiples
+        d.digits = 0;  // without room for the images the step kernels run
+        return;
+    }
     d.frag = b;
     d.F32 = (float *)b;
     d.F16 = (uint16_t *)(b + 4 * e32);

@@ -193,3 +193,43 @@ def test_only_graphs_of_the_one_spin_per_lane_kernel_get_its_lane_order(run, n, 
     ok(lib.qaia_problem_destroy(p))
     assert fake.fake_in_use() == 0
     """, n, degree, int(order))
+
+
+def test_problem_without_room_for_the_images_of_small_dense_graphs(run):
+    """The fragment and digit images only make calls faster: where their allocation
+    fails, the problem is created without them and the step kernels run."""
+    run("""
+    n, m = 512, 3
+    fake.fake_limit(4 << 20)  # the dense images take 3 MiB, their fragments and digits 8
+    for largest, variant in ((LARGE, BSB), (SMALL, DSB)):
+        p = problem(n, m, *edges(n, 1.1), largest)
+        assert fake.fake_sticky() == 0
+        sample(p, n, m, 64, 64, Schedule(variant, FP32, 7, STAGED, 0.5, 1.0, 0.1, 0.0, 1, 0))
+        assert count("dense_step_staged") + count("dense_thin") == 7
+        assert count("resident_kernel") + count("digits_kernel") == 0
+        batch([(p, n, m, 8, 8)] * 2, Schedule(variant, FP32, 7, AUTO, 0.5, 1.0, 0.1, 0.0, 1, 0))
+        assert count("dense_batch_step_staged") == 7 and count("resident_kernel") + count("digits_kernel") == 0
+        ok(lib.qaia_problem_destroy(p))
+    assert fake.fake_in_use() == 0
+    """)
+
+
+def test_problem_without_room_for_the_cut_images(run):
+    """Nor does a problem need the digit matrices of the cuts: the edges are walked."""
+    run("""
+    n, m = 512, 8
+    fake.fake_limit(5 << 20)  # the weights take 4 MiB, the matrices 6
+    p = problem(n, m, *edges(n, 1.1), LARGE)
+    assert fake.fake_sticky() == 0
+    spins, obj = buffers(n, m, 100)
+    fake.fake_clear()
+    ok(lib.qaia_evaluate(p, ptr(spins), C.c_int64(100), ptr(obj), None))
+    assert count("eval_tile_kernel") == 1 and count("cut_kernel") == 0
+    ok(lib.qaia_problem_destroy(p))
+    assert fake.fake_in_use() == 0
+    fake.fake_limit(3 << 20)  # the weights themselves do not fit
+    w = np.ones((m, edges(n, 1.1)[0].size), np.int32)
+    u, v = edges(n, 1.1)
+    rc = lib.qaia_problem_create(n, m, C.c_int64(u.size), ptr(u), ptr(v), ptr(w), 16, 0, C.byref(C.c_void_p()))
+    assert rc == 3 and fake.fake_in_use() == 0
+    """)
