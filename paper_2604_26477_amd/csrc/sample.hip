@@ -719,11 +719,27 @@ __global__ __launch_bounds__(kBlock) void eval_tile_kernel(
     }
 }
 
+// Whether a thread per sample that walks the edges is done before the matrix form.
+// The images are there from a density of 1/32 on, but the matrix form pays for whole
+// tiles of 32 spins: its four waves take row tiles x groups of three digit matrices in
+// rounds of 4.1e-5 us per sample, the walk 0.7 to 1.3e-6 us per sample and edge.  For
+// fewer samples the walk is bound by its chain of loads (0.3 to 0.47 us per edge) and
+// loses.  Walk against matrices, 570 000 samples: 65 nodes of degree 3, m = 4 68 / 79 us,
+// 73 nodes, m = 4 75 / 79, m = 8 113 / 145, 70 nodes, m = 3 69 / 72, 64 nodes, m = 4
+// 67 / 56; 100 000 samples of the first and third 28 / 19, 44 / 33.
+static bool walk_pays(const Problem &p, int64_t count) {
+    if (p.E > 4096) return false;
+    const double c = (double)count / 570000.0;
+    const int rounds = (p.cut.T * ((p.m * p.cut.L + 2) / 3) + 3) / 4;
+    const double walk = (double)p.E * std::max(0.24 + 0.029 * p.m, (0.55 + 0.095 * p.m) * c);
+    return walk < 8.0 + 23.2 * c * rounds;
+}
+
 void launch_evaluate(const Problem &p, const uint64_t *spins, int64_t count, int64_t *obj,
                      hipStream_t st) {
     if (count == 0) return;
     QAIA_CHECK(p.m <= 8, QAIA_UNSUPPORTED, "evaluation supports at most 8 objectives");
-    if (p.cut.ok) {
+    if (p.cut.ok && !walk_pays(p, count)) {
         launch_cut(p, spins, count, obj, st);
         return;
     }

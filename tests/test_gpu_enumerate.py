@@ -160,3 +160,20 @@ def test_dirichlet_weights_uniform_on_simplex(q, m):
         ks = np.max(np.abs(cdf - np.arange(1, n + 1) / n))
         assert ks < 1.95 / np.sqrt(n), (k, ks)
     assert abs(w.mean() - 1.0 / m) < 1e-3
+
+
+@pytest.mark.parametrize("n,m,bits", [(65, 4, 20), (73, 8, 20), (57, 3, 31)])
+def test_evaluate_many_samples_of_few_edges(q, n, m, bits):
+    """Many samples of a graph just past the line of the digit matrices walk the
+    edges, fewer take the matrices: the same cuts, and the oracle's."""
+    import torch
+    rng = np.random.default_rng(n)
+    base = wl.random_instance(n, m, "deg3", seed=1600 + n)
+    w = rng.integers(-2**bits + 1, 2**bits, size=(m, base.num_edges))
+    inst = wl.Instance(n, m, base.edge_u, base.edge_v, w.astype(np.int32))
+    prob = q.problem_from_instance(inst)
+    spins = q.qaia_random_spins(n, 570_000, seed=11)
+    obj = q.qaia_evaluate(prob, spins)
+    assert torch.equal(obj, torch.cat([q.qaia_evaluate(prob, s.contiguous()) for s in spins.split(9_999)]))
+    head = spins[:2000].cpu().numpy()
+    assert np.array_equal(obj[:2000].cpu().numpy(), oracle.cut_values(inst, unpack_spins(head, n)))

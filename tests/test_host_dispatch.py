@@ -233,3 +233,22 @@ def test_problem_without_room_for_the_cut_images(run):
     rc = lib.qaia_problem_create(n, m, C.c_int64(u.size), ptr(u), ptr(v), ptr(w), 16, 0, C.byref(C.c_void_p()))
     assert rc == 3 and fake.fake_in_use() == 0
     """)
+
+
+# ---------------------------------------------------------------- cuts
+
+@pytest.mark.parametrize("n,extra,m,count,walk", [(73, 12, 8, 570_000, True), (73, 12, 8, 100_000, False), (65, 10, 4, 570_000, True),
+                                                  (65, 10, 4, 1000, False), (64, 10, 4, 570_000, False), (73, 300, 8, 570_000, False)])
+def test_cuts_of_few_edges_and_many_samples_walk_the_edges(run, n, extra, m, count, walk):
+    """Graphs with cut images still walk their edges where many samples make that shorter."""
+    run("""
+    n, extra, m, samples, walk = (int(x) for x in sys.argv[3:8])
+    u, v = ring(n)
+    a, b = np.triu_indices(n, 2)
+    u, v = np.concatenate([u, a[:extra].astype(np.int32)]), np.concatenate([v, b[:extra].astype(np.int32)])
+    p = problem(n, m, u, v, LARGE)
+    spins, obj = buffers(n, m, samples)
+    fake.fake_clear()
+    ok(lib.qaia_evaluate(p, ptr(spins), C.c_int64(samples), ptr(obj), None))
+    assert (count("eval_thread_kernel"), count("cut_kernel")) == (walk, 1 - walk)
+    """, n, extra, m, count, int(walk))
