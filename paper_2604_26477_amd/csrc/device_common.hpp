@@ -36,11 +36,13 @@ __device__ __forceinline__ uint64_t init_counter(uint64_t g, int n, int i, int c
 // Standard normal for noise injection (Eq. 10): Box-Muller on two 24-bit
 // uniforms of one draw from the keyed stream.  Noise-injected sampling is
 // bound by the VALU work of this function, so it is written for its own
-// arguments only, with the same values as sqrtf(-2 logf(u1)) cosf(2 pi u2) for
-// every one of the 2^24 u1 and u2:
-//  - ln u = log2 u * ln 2 with ln 2 in two floats (the hardware log2, a product
-//    and its exact remainder); u1 is in [2^-24, 1], so there is no denormal or
-//    infinity to look for (22 -> 5 operations with the library's logf);
+// arguments only, with the same values as sqrtf(-2 logf(u1)) cosf(2 pi u2)
+// (compared on the device for all 2^24 u1, and for all 2^24 u2):
+//  - ln u = log2 u * ln 2 in the steps, and with the two floats of ln 2, of the
+//    compiler's own logf (the hardware log2, its product with the high float, that
+//    product's remainder, the low float, summed with fused operations), which is
+//    what the same values take; u1 is in [2^-24, 1], so there is no denormal or
+//    infinity to look for (22 -> 5 operations);
 //  - sqrt by one correction of x rsq(x) from its exact residual, x in
 //    [0, 33.3]; the bound on rsq makes sqrt(0) = 0 (20 -> 6);
 //  - the angle is below 2 pi, which is stated to the compiler: it drops the
@@ -55,8 +57,8 @@ __device__ __forceinline__ float noise_from(uint64_t z) {
     const float u2 = (float)(uint32_t)(bits & 0xffffffu) * 0x1p-24f;
     const float l2 = __builtin_amdgcn_logf(u1);
     const float ln2h = 0x1.62e42ep-1f, ln2l = 0x1.efa39ep-25f;  // ln 2 = ln2h + ln2l
-    const float pr = l2 * ln2h;
-    const float ln = pr + fmaf(l2, ln2l, fmaf(l2, ln2h, -pr));
+    // every fusion is written out: left to the compiler, the last sum's would depend on its flags
+    const float ln = fmaf(l2, ln2h, fmaf(l2, ln2l, fmaf(l2, ln2h, -(l2 * ln2h))));
     const float x = -2.0f * ln;
     const float rs = fminf(fabsf(__builtin_amdgcn_rsqf(x)), 0x1p60f);
     const float s0 = x * rs;

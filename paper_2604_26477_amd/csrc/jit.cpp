@@ -96,8 +96,7 @@ __device__ __forceinline__ float nzv(u64 seed, u64 idx) {
   float u1 = (float)((u32)(b >> 40) + 1u) * 0x1p-24f;
   float u2 = (float)(u32)(b & 0xffffffull) * 0x1p-24f;
   float l2 = __builtin_amdgcn_logf(u1), h = 0x1.62e42ep-1f, l = 0x1.efa39ep-25f;
-  float pr = l2 * h;
-  float x = -2.0f * (pr + __builtin_fmaf(l2, l, __builtin_fmaf(l2, h, -pr)));
+  float x = -2.0f * __builtin_fmaf(l2, h, __builtin_fmaf(l2, l, __builtin_fmaf(l2, h, -(l2 * h))));
   float rs = __builtin_fminf(__builtin_fabsf(__builtin_amdgcn_rsqf(x)), 0x1p60f);
   float s0 = x * rs;
   float angle = 6.2831853071795864769f * u2;
