@@ -38,7 +38,10 @@ constexpr int64_t kWideMax1 = (int64_t)10 * 64 * 1024, kWideMax4 = (int64_t)20 *
 // 32 768 replicas, V = 4: 5.9 us per step with 256 lanes, 7.1 with 512), and where
 // it is not, or where neighbour lists of more than eight take the registers, one
 // spin per lane (n = 512, 80 replicas: 0.29 against 0.37 us per step; n = 300,
-// degree up to 19, 32 768 replicas: 16 against 25).
+// degree up to 19, 32 768 replicas: 16 against 25).  With noise or tracing, which the
+// draws bind and which need whole groups side by side, several spins per lane
+// throughout (noise, 32 768 replicas, against the tiled kernel: n = 512, mean degree
+// 15, 301 -> 91 us per step; n = 1000, mean degree 12, 1091 -> 404, one wave per SIMD).
 int group_shape(int n, int maxdeg, int V, bool full, int64_t lanes) {
     if (n <= 64) return 0;
     if (n <= 128) return 1;
@@ -106,20 +109,20 @@ void launch_sparse_group(const Problem &p, int64_t W, int32_t R, const qaia_sche
     } else if (V == 1) {
         launch_group_v1(shape, dsb, p.max_degree, grid, block, a, st);
     } else {
-#define QAIA_V4(SHAPE, NTMAX, NPT)                                                                       \
-    case SHAPE:                                                                                          \
-        if (dsb) launch_group_deg<NTMAX, NPT, 4, true, false>(p.max_degree, grid, block, a, st);         \
-        else launch_group_deg<NTMAX, NPT, 4, false, false>(p.max_degree, grid, block, a, st);            \
+#define QAIA_V4(SHAPE, NTMAX, NPT, LONG)                                                               \
+    case SHAPE:                                                                                        \
+        if (dsb) launch_group_deg<NTMAX, NPT, 4, true, false, LONG>(p.max_degree, grid, block, a, st); \
+        else launch_group_deg<NTMAX, NPT, 4, false, false, LONG>(p.max_degree, grid, block, a, st);    \
         break;
         switch (shape) {
-            QAIA_V4(0, 64, 1)
-            QAIA_V4(1, 64, 2)
-            QAIA_V4(2, 64, 4)
-            QAIA_V4(3, 256, 2)
-            QAIA_V4(4, 256, 4)
-            QAIA_V4(5, 512, 1)
+            QAIA_V4(0, 64, 1, true)
+            QAIA_V4(1, 64, 2, true)
+            QAIA_V4(2, 64, 4, false)
+            QAIA_V4(3, 256, 2, false)
+            QAIA_V4(4, 256, 4, false)
+            QAIA_V4(5, 512, 1, true)
             default:
-            QAIA_V4(6, 512, 2)
+            QAIA_V4(6, 512, 2, true)
         }
 #undef QAIA_V4
     }

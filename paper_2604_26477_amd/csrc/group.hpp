@@ -308,12 +308,14 @@ __global__ __launch_bounds__(NTMAX) void group_kernel(GroupArgs a) {
     }
 }
 
-// One of the launches of group.hip: NTMAX x NPT lanes x spins, V replicas.
-template <int NTMAX, int NPT, int V, bool DSB, bool FULL>
+// One of the launches of group.hip: NTMAX x NPT lanes x spins, V replicas.  LONG: shapes
+// that lists of more than eight neighbours take.
+template <int NTMAX, int NPT, int V, bool DSB, bool FULL, bool LONG>
 void launch_group_deg(int maxdeg, dim3 grid, dim3 block, const GroupArgs &a, hipStream_t st) {
     if (maxdeg <= 3) hipLaunchKernelGGL((group_kernel<NTMAX, NPT, V, 3, DSB, FULL>), grid, block, 0, st, a);
     else if (maxdeg <= 8) hipLaunchKernelGGL((group_kernel<NTMAX, NPT, V, 8, DSB, FULL>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((group_kernel<NTMAX, NPT, V, 32, DSB, FULL>), grid, block, 0, st, a);
+    else if constexpr (LONG) hipLaunchKernelGGL((group_kernel<NTMAX, NPT, V, 32, DSB, FULL>), grid, block, 0, st, a);
+    else throw Error{QAIA_DEVICE_ERROR, "no kernel of this shape for so many neighbours"};  // group_shape picks none
 }
 
 void launch_group_v1(int shape, bool dsb, int maxdeg, dim3 grid, dim3 block, const GroupArgs &a, hipStream_t st);

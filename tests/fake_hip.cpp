@@ -28,6 +28,15 @@ void fake_limit(size_t bytes) { limit = bytes; }  // largest allocation that suc
 size_t fake_in_use() { return in_use; }
 int fake_sticky() { return sticky; }
 void fake_clear() { launched.clear(); }
+const char *fake_kernels(int of_launches) {  // names, one a line: of the launches so far, or of all kernels
+    static std::string all;
+    all.clear();
+    if (of_launches)
+        for (const std::string &s : launched) all += s + "\n";
+    else
+        for (const auto &kv : names) all += kv.second + "\n";
+    return all.c_str();
+}
 int fake_count(const char *part) {  // launches so far of kernels whose (mangled) name holds `part`
     int n = 0;
     for (const std::string &s : launched) n += s.find(part) != std::string::npos;

@@ -252,3 +252,27 @@ def test_cuts_of_few_edges_and_many_samples_walk_the_edges(run, n, extra, m, cou
     ok(lib.qaia_evaluate(p, ptr(spins), C.c_int64(samples), ptr(obj), None))
     assert (count("eval_thread_kernel"), count("cut_kernel")) == (walk, 1 - walk)
     """, n, extra, m, count, int(walk))
+
+
+def test_every_one_spin_per_lane_kernel_is_reached(run):
+    """No instance is built that no call launches: spins, degrees, replicas, noise
+    and variants on both sides of every rule of the choice."""
+    run("""
+    fake.fake_kernels.restype = C.c_char_p
+    names = lambda launched: {k for k in fake.fake_kernels(launched).decode().split() if "group_kernel" in k}
+    built, seen = names(0), set()
+    for n in (20, 100, 200, 400, 700):
+        for degree in (2, 6, 19):
+            u, v = ring(n)
+            if degree > 2:
+                u, v = np.concatenate([u, np.zeros(degree - 1, np.int32)]), np.concatenate([v, np.arange(2, degree + 1, dtype=np.int32)])
+            p = problem(n, 1, u, v, SMALL)
+            for lanes in (1 << 17, 600_000, 700_000, 1_500_000):
+                for R in (3, lanes // n):
+                    for variant in (BSB, DSB):
+                        for noise in (0.0, 0.1):
+                            s = Schedule(variant, FP32, 3, SPARSE_LDS, 0.5, 1.0, 0.1, noise, 1, 0)
+                            sample(p, n, 1, -(-lanes // n // R), R, s)
+                            seen |= names(1)
+    assert built and seen == built, sorted(built - seen)
+    """)
