@@ -42,7 +42,7 @@ namespace {
 
 constexpr int kB = 256;
 constexpr int kCols = 128;       // samples per block
-constexpr int kChunkTiles = 14;  // 32-spin tiles per chunk: 56 KB of LDS, and 8 KB of sums at m = 8
+constexpr int kChunkTiles = 14;  // 32-spin tiles per chunk: 56 KB of int8 spins, 7 KB of spin words, 8 KB of sums at m = 8
 constexpr int kGroup = 3;        // slices per item
 
 // One thread per (edge, objective): the digits of its weight into the upper

@@ -102,17 +102,23 @@ void launch_sparse_group(const Problem &p, int64_t W, int32_t R, const qaia_sche
     a.per_block = NT * gs.npt / n;
     const int64_t blocks = (a.groups + a.per_block - 1) / a.per_block;
     QAIA_CHECK(blocks <= INT32_MAX, QAIA_INVALID_ARGUMENT, "too many replicas for one launch");
+    // Several small groups in a wave: with few edges a lane per replica and objective reads
+    // out, since the whole wave would take those one after the other (calls of 60 steps: 2
+    // nodes, m = 8, 3200 replicas 122 -> 19 us; 12 nodes, m = 3, 10 000 27 -> 22; at the line,
+    // complete 12 nodes, m = 3, 3200 no difference).
+    const bool flat = shape == 0 && a.per_block > 1 &&
+                      p.E <= 4 * std::min<int64_t>(a.per_block, a.groups) * V * p.m;
     const dim3 grid((unsigned)blocks);
     const dim3 block(NT);
     if (full) {
-        launch_group_full(shape, dsb, p.max_degree, grid, block, a, st);
+        launch_group_full(shape, dsb, p.max_degree, flat, grid, block, a, st);
     } else if (V == 1) {
-        launch_group_v1(shape, dsb, p.max_degree, grid, block, a, st);
+        launch_group_v1(shape, dsb, p.max_degree, flat, grid, block, a, st);
     } else {
-#define QAIA_V4(SHAPE, NTMAX, NPT, LONG)                                                               \
-    case SHAPE:                                                                                        \
-        if (dsb) launch_group_deg<NTMAX, NPT, 4, true, false, LONG>(p.max_degree, grid, block, a, st); \
-        else launch_group_deg<NTMAX, NPT, 4, false, false, LONG>(p.max_degree, grid, block, a, st);    \
+#define QAIA_V4(SHAPE, NTMAX, NPT, LONG)                                                                     \
+    case SHAPE:                                                                                              \
+        if (dsb) launch_group_deg<NTMAX, NPT, 4, true, false, LONG>(p.max_degree, flat, grid, block, a, st); \
+        else launch_group_deg<NTMAX, NPT, 4, false, false, LONG>(p.max_degree, flat, grid, block, a, st);    \
         break;
         switch (shape) {
             QAIA_V4(0, 64, 1, true)

@@ -3,7 +3,10 @@
 //
 // A group's spins are spread over the NT lanes of a block, NPT spins per lane.
 // Each lane keeps x and y of its spins for all V replicas, its neighbours' LDS
-// places and the folded edge coefficients in registers; Phi (x for ballistic
+// places and the folded edge coefficients in registers (with four replicas and several
+// spins per lane of degree past 3 the compiler puts the coefficients into scratch, 80
+// to 272 bytes: it merges the last product of a chunk's two lengths, whose index then
+// varies); Phi (x for ballistic
 // SB, sgn x for discrete SB) of the V replicas sits in LDS as one vector per
 // spin, double buffered at a fixed distance, so that a neighbour's V values
 // are one read at an immediate offset: a 16-byte gather moves four replicas
@@ -13,8 +16,9 @@
 // Spins take lanes in order of falling degree, so a wave's 64 spins have nearly
 // equal degrees and its neighbour loop ends at the largest of them (a scalar
 // branch per neighbour).  Lanes below it add 0 times a neighbour, which changes no
-// value.  Groups of n <= 256 spins run in one wave and need no barrier at all:
-// LDS operations of a wave are in order.  Blocks of one wave with n <= 32 take
+// value.  Groups of up to 128 spins, and up to 256 where the GPU is full and lists
+// are short, run in one wave and need no barrier at all: LDS operations of a wave are
+// in order.  Blocks of one wave with n <= 32 take
 // several groups side by side.
 //
 // Every spin's update is the sequence of operations of the other sparse kernels
@@ -55,8 +59,10 @@ struct GroupArgs {
 
 // FULL: noise injection and tracing, which keep each spin's row and counters
 // in registers (V = 1).
+// FLAT: the read-out of several small groups in a wave (an instance of its own: the
+// place of the step loop in the code alone moves it by 2 %).
 // Blocks have up to NTMAX lanes.
-template <int NTMAX, int NPT, int V, int MAXDEG, bool DSB, bool FULL>
+template <int NTMAX, int NPT, int V, int MAXDEG, bool DSB, bool FULL, bool FLAT = false>
 __global__ __launch_bounds__(NTMAX) void group_kernel(GroupArgs a) {
     typedef typename Vec<V>::T VT;
     constexpr int SPAN = NTMAX * NPT;  // spins per buffer
@@ -226,36 +232,30 @@ __global__ __launch_bounds__(NTMAX) void group_kernel(GroupArgs a) {
             xs[(q * NT + tid) / n * n + node[q]] = s;
         }
     __syncthreads();
-    // Several small groups in a wave: a lane per (replica, objective) walks the edges,
-    // since the read-out below takes those one after the other (calls of 60 steps: 2
-    // nodes, m = 8, 3200 replicas 122 -> 19 us; 12 nodes, m = 3, 10 000 27 -> 22).
-    if constexpr (NTMAX == 64 && NPT == 1) {
-        const int64_t here = min((int64_t)a.per_block, a.groups - (int64_t)blockIdx.x * a.per_block);
-        if (E <= 4 * here * V * a.m) {
-            const float *xf = (const float *)xs;
-            for (int i = tid; i < a.per_block * V * a.m; i += NT) {
-                const int sr = i / a.m, k = i - sr * a.m, slot = sr / V, v = sr - slot * V;
-                const int64_t grp = (int64_t)blockIdx.x * a.per_block + slot;
-                if (grp >= a.groups) break;
-                const int64_t w = grp / a.groups_per_w;
-                const int r = (int)(grp - w * a.groups_per_w) * V + v;
-                if (r >= a.R) continue;
-                const bool valid = a.c0s[w] >= 0.0;
-                const float *s = xf + slot * n * V + v;
-                int64_t cut = 0;
+    if constexpr (FLAT) {  // a lane per (replica, objective) walks the edges
+        const float *xf = (const float *)xs;
+        for (int i = tid; i < a.per_block * V * a.m; i += NT) {
+            const int sr = i / a.m, k = i - sr * a.m, slot = sr / V, v = sr - slot * V;
+            const int64_t grp = (int64_t)blockIdx.x * a.per_block + slot;
+            if (grp >= a.groups) break;
+            const int64_t w = grp / a.groups_per_w;
+            const int r = (int)(grp - w * a.groups_per_w) * V + v;
+            if (r >= a.R) continue;
+            const bool valid = a.c0s[w] >= 0.0;
+            const float *s = xf + slot * n * V + v;
+            int64_t cut = 0;
 #pragma unroll 4
-                for (int64_t e = 0; e < E; ++e)
-                    cut += s[a.eu[e] * V] != s[a.ev[e] * V] ? (int64_t)a.Wt[(int64_t)k * E + e] : 0;
-                a.obj[(w * a.R + r) * a.m + k] = valid ? cut : 0;
-                if (k == 0) {
-                    uint64_t bits = 0;
+            for (int64_t e = 0; e < E; ++e)
+                cut += s[a.eu[e] * V] != s[a.ev[e] * V] ? (int64_t)a.Wt[(int64_t)k * E + e] : 0;
+            a.obj[(w * a.R + r) * a.m + k] = valid ? cut : 0;
+            if (k == 0) {
+                uint64_t bits = 0;
 #pragma unroll 4
-                    for (int j = 0; j < n; ++j) bits |= (uint64_t)(s[j * V] < 0.0f) << j;
-                    a.spins[w * a.R + r] = valid ? bits : 0ull;
-                }
+                for (int j = 0; j < n; ++j) bits |= (uint64_t)(s[j * V] < 0.0f) << j;
+                a.spins[w * a.R + r] = valid ? bits : 0ull;
             }
-            return;
         }
+        return;
     }
     for (int slot = 0; slot < a.per_block; ++slot) {
         const int64_t grp = (int64_t)blockIdx.x * a.per_block + slot;
@@ -311,14 +311,21 @@ __global__ __launch_bounds__(NTMAX) void group_kernel(GroupArgs a) {
 // One of the launches of group.hip: NTMAX x NPT lanes x spins, V replicas.  LONG: shapes
 // that lists of more than eight neighbours take.
 template <int NTMAX, int NPT, int V, bool DSB, bool FULL, bool LONG>
-void launch_group_deg(int maxdeg, dim3 grid, dim3 block, const GroupArgs &a, hipStream_t st) {
+void launch_group_deg(int maxdeg, bool flat, dim3 grid, dim3 block, const GroupArgs &a, hipStream_t st) {
+    if constexpr (NTMAX == 64 && NPT == 1)
+        if (flat) {
+            if (maxdeg <= 3) hipLaunchKernelGGL((group_kernel<NTMAX, NPT, V, 3, DSB, FULL, true>), grid, block, 0, st, a);
+            else if (maxdeg <= 8) hipLaunchKernelGGL((group_kernel<NTMAX, NPT, V, 8, DSB, FULL, true>), grid, block, 0, st, a);
+            else hipLaunchKernelGGL((group_kernel<NTMAX, NPT, V, 32, DSB, FULL, true>), grid, block, 0, st, a);
+            return;
+        }
     if (maxdeg <= 3) hipLaunchKernelGGL((group_kernel<NTMAX, NPT, V, 3, DSB, FULL>), grid, block, 0, st, a);
     else if (maxdeg <= 8) hipLaunchKernelGGL((group_kernel<NTMAX, NPT, V, 8, DSB, FULL>), grid, block, 0, st, a);
     else if constexpr (LONG) hipLaunchKernelGGL((group_kernel<NTMAX, NPT, V, 32, DSB, FULL>), grid, block, 0, st, a);
     else throw Error{QAIA_DEVICE_ERROR, "no kernel of this shape for so many neighbours"};  // group_shape picks none
 }
 
-void launch_group_v1(int shape, bool dsb, int maxdeg, dim3 grid, dim3 block, const GroupArgs &a, hipStream_t st);
-void launch_group_full(int shape, bool dsb, int maxdeg, dim3 grid, dim3 block, const GroupArgs &a, hipStream_t st);
+void launch_group_v1(int shape, bool dsb, int maxdeg, bool flat, dim3 grid, dim3 block, const GroupArgs &a, hipStream_t st);
+void launch_group_full(int shape, bool dsb, int maxdeg, bool flat, dim3 grid, dim3 block, const GroupArgs &a, hipStream_t st);
 
 }  // namespace qaia

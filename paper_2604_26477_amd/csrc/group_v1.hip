@@ -3,11 +3,11 @@
 
 namespace qaia {
 
-void launch_group_v1(int shape, bool dsb, int maxdeg, dim3 grid, dim3 block, const GroupArgs &a, hipStream_t st) {
-#define QAIA_GROUP(SHAPE, NTMAX, NPT, LONG)                                                      \
-    case SHAPE:                                                                                  \
-        if (dsb) launch_group_deg<NTMAX, NPT, 1, true, false, LONG>(maxdeg, grid, block, a, st); \
-        else launch_group_deg<NTMAX, NPT, 1, false, false, LONG>(maxdeg, grid, block, a, st);    \
+void launch_group_v1(int shape, bool dsb, int maxdeg, bool flat, dim3 grid, dim3 block, const GroupArgs &a, hipStream_t st) {
+#define QAIA_GROUP(SHAPE, NTMAX, NPT, LONG)                                                            \
+    case SHAPE:                                                                                        \
+        if (dsb) launch_group_deg<NTMAX, NPT, 1, true, false, LONG>(maxdeg, flat, grid, block, a, st); \
+        else launch_group_deg<NTMAX, NPT, 1, false, false, LONG>(maxdeg, flat, grid, block, a, st);    \
         break;
     switch (shape) {
         QAIA_GROUP(0, 64, 1, true)

@@ -261,18 +261,19 @@ def test_every_one_spin_per_lane_kernel_is_reached(run):
     fake.fake_kernels.restype = C.c_char_p
     names = lambda launched: {k for k in fake.fake_kernels(launched).decode().split() if "group_kernel" in k}
     built, seen = names(0), set()
-    for n in (20, 100, 200, 400, 700):
+    for n in (20, 40, 100, 200, 400, 700):
+        m = 8 if n == 20 else 1  # few edges per replica and objective: the read-out of several groups in a wave
         for degree in (2, 6, 19):
             u, v = ring(n)
             if degree > 2:
                 u, v = np.concatenate([u, np.zeros(degree - 1, np.int32)]), np.concatenate([v, np.arange(2, degree + 1, dtype=np.int32)])
-            p = problem(n, 1, u, v, SMALL)
+            p = problem(n, m, u, v, SMALL)
             for lanes in (1 << 17, 600_000, 700_000, 1_500_000):
                 for R in (3, lanes // n):
                     for variant in (BSB, DSB):
                         for noise in (0.0, 0.1):
                             s = Schedule(variant, FP32, 3, SPARSE_LDS, 0.5, 1.0, 0.1, noise, 1, 0)
-                            sample(p, n, 1, -(-lanes // n // R), R, s)
+                            sample(p, n, m, -(-lanes // n // R), R, s)
                             seen |= names(1)
     assert built and seen == built, sorted(built - seen)
     """)
