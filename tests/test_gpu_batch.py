@@ -244,3 +244,15 @@ def test_batch_of_staged_items_up_to_512_nodes(q, count, variant, prec, alpha):
     sizes = [(512, 4), (300, 2), (257, 1), (130, 3), (70, 4), (31, 2), (384, 3), (200, 1)]
     specs = [(*sizes[i % len(sizes)], "p0.3", 1 + i % 3, 5 + i % 7) for i in range(count)]
     _batch_equals_per_item_calls(q, specs, variant, prec, alpha, 12)
+
+
+@pytest.mark.parametrize("variant,prec,alpha", [("bsb", "fp32", 0.0), ("dsb", "fp32", 0.1), ("dsb", "bf16", 0.0),
+                                                ("dsb", "fp8", 0.1)])
+def test_batch_of_staged_items_past_512_nodes(q, variant, prec, alpha):
+    """The grouped staged step, which all staged items past 512 nodes share: at
+    least two items for each number of objectives, ragged columns and sizes (starts
+    on multiples of eight tiles), an item without weight vectors and a small one."""
+    specs = [(520, 1, "p0.1", 3, 50), (640, 1, "p0.05", 1, 7), (600, 2, "p0.1", 2, 65), (513, 2, "p0.1", 5, 30),
+             (640, 3, "p0.05", 1, 129), (520, 3, "p0.1", 0, 8), (600, 3, "p0.05", 4, 9), (513, 4, "p0.1", 2, 11),
+             (600, 4, "p0.05", 3, 43), (100, 4, "p0.3", 2, 9)]
+    _batch_equals_per_item_calls(q, specs, variant, prec, alpha, 9)
