@@ -281,7 +281,7 @@ __global__ __launch_bounds__(kT) void mlp_tile_kernel(const uint16_t *__restrict
 // when read and, with the pitch of 516, when filled along k.
 // Bound by the vector unit: 256 gelus of some 57 instructions per sample, 28 us
 // for 65 536 samples if nothing else ran; the MFMAs lie between them.  That many
-// samples of twelve inputs: 133 us with a block of four waves per 32, now 46.
+// samples of twelve inputs: 123 to 133 us with a block of four waves per 32, now 46 to 48.
 constexpr int kRWaves = 8;
 constexpr int kW2Pitch = 4 * kH + 4;
 constexpr int kW2Parity = 16 * kW2Pitch + 16;

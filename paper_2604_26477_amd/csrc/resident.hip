@@ -189,7 +189,9 @@ __device__ __forceinline__ void resident_body(const ResidentArgs &a, char *lds) 
 
     // Fragment (k, r, q) through a buffer descriptor: a scalar offset and one
     // register for the lane (with ordinary loads the compiler keeps M 64-bit
-    // addresses per lane, which spilled at M = 4 and sixteen waves).
+    // addresses per lane, which spilled at M = 4 and sixteen waves: 146 us per step,
+    // now 120; the 2 to 19 registers that are still too few there are read back from
+    // scratch once per step, not in the loop over the fragments).
     constexpr int FB = 64 * (int)sizeof(V);  // bytes of a fragment
     const int kstride = a.tiles * groups * FB;
     const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)a.J, 0, M * kstride, 0x00027000);
@@ -294,7 +296,8 @@ __global__ __launch_bounds__(WAVES * 64) void resident_kernel(ResidentArgs a) {
 // them; the sum is converted exactly and enters the same update.  Integers leave
 // no rounding to differ: trajectories are those of the FP32 product bit for bit.
 // The digits of a wave's 32 rows stream from L2 as in the other kernel, Phi
-// stays in registers for the step (up to 256 spins).
+// stays in registers for the step (up to 192 spins; up to 256 it is read from LDS for
+// every digit, and three digits keep 14 to 32 registers in scratch, outside the MFMAs).
 // Bound by the vector instructions of the draws and the update: complete n = 100,
 // m = 3, 570 000 columns with noise: 430 us per step on the FP32 product (290 of
 // them MFMA, which there does not overlap with vector work), now 148.
