@@ -241,10 +241,13 @@ int digits_for(const std::vector<int32_t> &W) {
 
 }  // namespace
 
-// Built where the matrix form does less work than a walk over the edges: per
-// sample the walk costs about 14 vector instructions on each edge, the MFMAs
-// S / 1024 cycles on each pair of spins, so at S = 9 they are even at a density
-// near 2 %; the line is drawn at 1/32 of the pairs.  Images of at most 512 MiB.
+// Built where the matrix form does less work than a walk over the edges: at S = 9 the
+// walk's instructions per edge and the MFMAs' cycles per pair of spins are even at a
+// density near 2 %, and the line is drawn at 1/32 of the pairs.  Walk against matrices
+// there: 129 nodes, m = 4, 10 000 samples 93 / 15 us, 570 000 244 / 143; 1024 nodes, m = 3,
+// 10 000 124 / 66; 73 nodes of degree 3, m = 4, 10 000 29 / 15, 570 000 75 / 79, which is why
+// launch_evaluate still walks the edges of small graphs for many samples.  Images of at
+// most 512 MiB.
 void cut_build(Problem &p) {
     CutImages &c = p.cut;
     if (p.E < 64 || p.E < (int64_t)p.n * p.n / 64) return;
